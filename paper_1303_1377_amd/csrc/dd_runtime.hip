@@ -271,6 +271,8 @@ struct dd_ctx {
     void* bicg_ws = nullptr;     // odd-even BiCGStab vectors (levels arena; cleared with it)
     int bicg_prec = 0;
     void* id_ws = nullptr;       // inexact-deflation vectors (levels arena; cleared with it)
+    Arena dstage;                // the two FP64 spinors of dd_apply(DD_OP_D) on an unconfigured context
+    cx<double>* dsv = nullptr;   // (allocated by the first such call, given back by dd_configure)
     void* scratch = nullptr;     // device address of this GPU's `scratch` array (dd_apply_D_noalloc)
     std::string scratch_err;     // why it is unavailable, if it is
     int sched = SCHED_LDS | SCHED_XCD | SCHED_GRAPH;   // launch schedule (SCHED_* flags)
@@ -1992,6 +1994,8 @@ static void configure_impl(dd_ctx* C, const dd_params* pin) {
     C->H64.reset();
     C->H32.reset();
     C->levels.release();
+    C->dstage.release();
+    C->dsv = nullptr;
     C->configured = false;
     C->have_setup = false;
     C->stream = dd_ctx::StreamSlots{};
@@ -2540,7 +2544,7 @@ dd_status dd_time_kernel(dd_ctx* ctx, int cls, int reps, double* avg_ms) {
     ABI_END(ctx)
 }
 
-long long dd_device_bytes(const dd_ctx* ctx) { return ctx ? ctx->fields.bytes + ctx->levels.bytes : 0; }
+long long dd_device_bytes(const dd_ctx* ctx) { return ctx ? ctx->fields.bytes + ctx->levels.bytes + ctx->dstage.bytes : 0; }
 
 // op on k vectors (canonical [k][vol][nd] in and out) as one batch
 template <class T>
@@ -2708,10 +2712,12 @@ dd_status dd_apply(dd_ctx* ctx, int op, int level, int arg, const double* in, do
     if (!in || !out) fail(DD_EINVAL, "NULL vector");
     if (!ctx->configured) {
         if (op == DD_OP_D && level == 0) {
+            // staging kept on the context: allocating and freeing 2 x 403 MB on
+            // each call took 21 of 22.6 ms at 64x32^3
             const long n = 24L * ctx->g0.vh;
-            Arena tmp;
-            cx<double>* a = tmp.get<cx<double>>(n);
-            cx<double>* b = tmp.get<cx<double>>(n);
+            if (!ctx->dsv) ctx->dsv = ctx->dstage.get<cx<double>>(2 * (size_t)n);
+            cx<double>* a = ctx->dsv;
+            cx<double>* b = ctx->dsv + n;
             fine_import_spinor<double>(ctx->g0, in, a, ctx->s);
             fine_dirac<double>(fine_op<double>(ctx), a, b, ctx->s);
             fine_export_spinor<double>(ctx->g0, b, out, ctx->s);
