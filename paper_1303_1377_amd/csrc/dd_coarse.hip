@@ -9,6 +9,8 @@
 // Vectors are [parity][layout index][nd] (a site's unknowns contiguous);
 // operator blocks are column-major so that the thread owning row r reads
 // consecutive addresses across the wavefront.
+#include <algorithm>
+#include <mutex>
 #include <stdexcept>
 #include <type_traits>
 
@@ -1150,587 +1152,440 @@ void coarse_shift_diag(const Geom& g, int nd, double dm, cx<T>* M, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// coarse SAP half sweep (same algebra as the fine kernel, dense site blocks):
-// workgroup = one block, thread = (local site l, row r) for both parities.
+// Coarse SAP half sweep (the algebra of the fine kernel on dense site blocks):
+//   z_e <- Minv_e (b_e - H z)                 (z_e + t0, t0 = A_ee^{-1} r_e)
+//   rho  = b_o - M0_o z_o - H z               (with the new z_e: r_o - H_int t0)
+//   MR on M0_o - H_int Minv_e H_int from e_o = 0
+//   z_e -= Minv_e H_int e_o,  z_o += e_o
+// One workgroup per (block, group of KR right-hand sides).
+//
+// Bound: a 2^4 block of nd = 40 applies 470 blocks of nd x nd per half sweep
+// (6 MB in FP32), in 17 dependent phases; nothing of it fits on chip, so the
+// blocks stream from L2 / MALL and a phase is as fast as the loads the
+// workgroup keeps in flight.  One row per thread (320 threads, 8-byte loads,
+// a serial walk over a site's columns) kept too few: 2.2 TB/s with one
+// workgroup per CU.  Here a phase is one product with many columns at once:
+// LC = nd / RPL lanes read a block column as 16-byte words (RPL rows per
+// lane), `parts` such lane groups share the panel of one site (group p takes
+// the columns p, p + parts, ..., so neighbouring groups read neighbouring
+// columns), every lane loads U columns before it uses the first, and the
+// partial rows meet in LDS.  Vectors are staged in LDS as [site][row][KR], one
+// aligned read per column for all KR.  The hops of the residual are staged for
+// all directions at once (in rounds of `H` where LDS is short); the new z_e is
+// stored before the odd residual reads it, which makes H z + H_int t0 one pass.
+// Per half sweep, before -> now (4 MR steps): 64x32^3 level 1 (16x8^3, nd 40,
+// FP32, 4 RHS) 823 -> 306 us, 5 TB/s; 48x24^3 level 1 (2x3^3 blocks from
+// tables, FP32, 4 RHS) 834 -> 397 us, 6 TB/s; 32x16^3 level 1 (FP16 storage,
+// 1 RHS, 16 workgroups) 253 -> 94 us.
 // ---------------------------------------------------------------------------
-// row r of a column-major block times v; block entries and v are loaded in
-// batches of RA_BATCH (many loads in flight, the sum still in column order)
-// (a 4-byte complex -- FP16 storage -- is loaded as one 32-bit word and
-// converted after the batch: converting each half as it arrives would make the
-// compiler wait for every load in turn)
-template <class S>
-using cx_word = typename std::conditional<sizeof(cx<S>) == 4, unsigned int, cx<S>>::type;
+static constexpr int CS_NT = 1024;
+static constexpr int CS_PARTS = 12;   // lane groups that share a site's columns, at most
+static constexpr size_t CS_LDS = 150 * 1024;   // of the CU's 160 KB
 
-template <class T, class S, int RA_BATCH>
-__device__ __forceinline__ cx<T> row_apply(const cx<S>* __restrict__ A, int nd, int r, const cx<T>* v) {
-    using W = cx_word<S>;
-    const W* Aw = reinterpret_cast<const W*>(A);
-    cx<T> s = czero<T>();
-    for (int c0 = 0; c0 < nd; c0 += RA_BATCH) {
-        W a[RA_BATCH];
-        cx<T> x[RA_BATCH];
+// rows of a block column in one load; KR vector entries at one row
+template <class S, int RPL> struct alignas(sizeof(cx<S>) * RPL) RowPack { cx<S> v[RPL]; };
+template <class T, int KR> struct alignas(sizeof(cx<T>) * KR > 16 ? 16 : sizeof(cx<T>) * KR) RhsPack { cx<T> v[KR]; };
+
+// BIG: blocks of many sites with few unknowns, whose neighbour table does not
+// fit in LDS beside the fields: neighbours are found again where they are read
+template <class T, class S, int KR, int RPL, int NV, bool BIG>
+__global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const int* __restrict__ blocks, SapTab tab, int bv,
+                                                      const cx<T>* __restrict__ b, cx<T>* __restrict__ z, int mr_steps,
+                                                      long ld, int nr, Mask mk, int parts, int H) {
+    using RP = RowPack<S, RPL>;
+    using XP = RhsPack<T, KR>;
+    const int q0 = blockIdx.y * KR;
+    unsigned on = 0;
 #pragma unroll
-        for (int u = 0; u < RA_BATCH; u++) {
-            const bool in = c0 + u < nd;
-            a[u] = in ? Aw[(size_t)(c0 + u) * nd + r] : W{};
-            x[u] = in ? v[c0 + u] : czero<T>();
-        }
-#pragma unroll
-        for (int u = 0; u < RA_BATCH; u++)
-            if (c0 + u < nd) s += ccast<T>(__builtin_bit_cast(cx<S>, a[u])) * x[u];
+    for (int q = 0; q < KR; q++)
+        if (q0 + q < nr && mk.on(q0 + q)) on |= 1u << q;
+    if (!on) return;
+    b += (size_t)q0 * ld;
+    z += (size_t)q0 * ld;
+    extern __shared__ __align__(16) char smem_raw[];
+    const Geom g = op.g;
+    const int nd = op.nd, nt = blockDim.x, t = threadIdx.x;
+    const int F = bv * nd * KR;                          // entries of one block field
+    cx<T>* so = reinterpret_cast<cx<T>*>(smem_raw);      // odd-site field
+    cx<T>* se = so + F;                                  // even-site field
+    cx<T>* sg = se + F;                                  // staged hop inputs [H][F]
+    cx<T>* pr = sg + (size_t)H * F;                      // partial rows [parts][F]
+    cx<T>* zero = pr + (size_t)parts * F;                // KR zeros (columns past a group's last)
+    double* red = reinterpret_cast<double*>(zero + 2 * KR);   // [waves][KR][3]
+    int* sidx = reinterpret_cast<int*>(red + 3 * KR * (nt >> 6));   // [2][bv] layout index of a site
+    int* cnt = sidx + 2 * bv;                            // [2][bv] inner hops of a site
+    unsigned short* lst = reinterpret_cast<unsigned short*>(cnt + 2 * bv);   // [2][bv][8] slot | place << 4
+    int* nbg = reinterpret_cast<int*>(lst + 16 * bv);    // [2][8][bv] layout index of its neighbours (not BIG)
+    const int blk = blocks[blockIdx.x];
+    if (t < KR) zero[t] = czero<T>();
+    auto neighbour = [&](int p, int l, int k) {
+        int x[4];
+        cb_coords(g, p, sidx[p * bv + l], x);
+        return nb_index_sel(g, x, k);
+    };
+    for (int e = t; e < 2 * bv; e += nt) {
+        const int p = e / bv, l = e - p * bv;
+        sidx[e] = tab.bv ? tab.sites[((size_t)blk * 2 + p) * bv + l] : (blk << g.lbvh) + l;
     }
+    __syncthreads();
+    for (int e = t; e < 16 * bv; e += nt) {
+        const int l = e % bv, k = (e / bv) & 7, p = e / (8 * bv);
+        const int j = neighbour(p, l, k);
+        if (!BIG) nbg[e] = j;
+        int place;
+        if (tab.bv) {
+            const size_t gy = (size_t)(1 - p) * g.vh + j;
+            place = (tab.of[gy] == blk) ? tab.loc[gy] : -1;
+        } else {
+            place = ((j >> g.lbvh) == blk) ? j - (blk << g.lbvh) : -1;
+        }
+        lst[(p * bv + l) * 8 + k] = place < 0 ? 0 : (1 + k) | (place << 4);   // slot 0: leaves the block
+    }
+    __syncthreads();
+    for (int e = t; e < 2 * bv; e += nt) {
+        int n = 0;
+        for (int k = 0; k < 8; k++) {
+            const unsigned short w = lst[e * 8 + k];
+            if (w) lst[e * 8 + n++] = w;
+        }
+        cnt[e] = n;
+    }
+    // the thread's share of a block field: entries t, t + nt, ... (RHS t % KR)
+    int vg[NV];              // vector offset of the entry within one parity of one RHS
+    const int myq = t % KR;
+    const bool myon = (on >> myq) & 1u;
+    auto field = [&](int p, int u) {   // whole-vector offset of entry u at parity p
+        const int v = t + u * nt, l = v / (nd * KR);
+        return (size_t)myq * ld + ((size_t)p * g.vh + sidx[p * bv + l]) * nd + vg[u];
+    };
+#pragma unroll
+    for (int u = 0; u < NV; u++) vg[u] = ((t + u * nt) / KR) % nd;
+    __syncthreads();
+    const size_t nn = (size_t)nd * nd;
+    const int LC = nd / RPL, NG = nt / LC;
+    const int grp = t / LC, r0 = (t - grp * LC) * RPL;
+    constexpr int U = sizeof(T) == 8 || RPL * KR > 8 ? 3 : 4;
+    // partial rows of a product, for the lane groups' (site, part) tasks:
+    // entry e < count(l) of site l reads the block at base(l) + slot nn and the vector at offset xo
+    auto product = [&](auto&& base, auto&& count, auto&& entry) {
+        for (int task = grp; task < bv * parts && grp < NG; task += NG) {
+            const int l = task / parts, part = task - l * parts;
+            const cx<S>* A = base(l) + r0;
+            const int n = count(l);
+            cx<T> acc[RPL][KR];
+#pragma unroll
+            for (int r = 0; r < RPL; r++)
+#pragma unroll
+                for (int q = 0; q < KR; q++) acc[r][q] = czero<T>();
+            // the group's columns part, part + parts, ... of every entry, U at a
+            // time; the next U are loaded while the current ones multiply
+            const int nc = (nd - part + parts - 1) / parts;
+            int e = 0, i0 = 0;
+            auto fetch = [&](RP (&a)[U], int& xo) -> int {
+                if (e >= n) return 0;
+                int slot, x0;
+                entry(l, e, slot, x0);
+                const int c = part + i0 * parts, m = min(U, nc - i0);
+                const cx<S>* pa = A + (slot * (int)nn + c * nd);
+                xo = x0 + c * KR;
+#pragma unroll
+                for (int u = 0; u < U; u++) a[u] = *reinterpret_cast<const RP*>(pa + (u < m ? u * (parts * nd) : 0));
+                i0 += U;
+                if (i0 >= nc) { i0 = 0; e++; }
+                return m;
+            };
+            auto use = [&](const RP (&a)[U], int xo, int m) {
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const XP x = *reinterpret_cast<const XP*>(so + (u < m ? xo + u * (parts * KR) : (int)(zero - so)));
+#pragma unroll
+                    for (int r = 0; r < RPL; r++) {
+                        const cx<T> ar = ccast<T>(a[u].v[r]);
+#pragma unroll
+                        for (int q = 0; q < KR; q++) cmac(acc[r][q], ar, x.v[q]);
+                    }
+                }
+            };
+            RP a0[U], a1[U];
+            int x0 = 0, x1 = 0, m0 = fetch(a0, x0);
+            while (m0) {
+                const int m1 = fetch(a1, x1);
+                use(a0, x0, m0);
+                if (!m1) break;
+                m0 = fetch(a0, x0);
+                use(a1, x1, m1);
+            }
+            cx<T>* o = pr + (size_t)part * F + (size_t)(l * nd + r0) * KR;
+#pragma unroll
+            for (int r = 0; r < RPL; r++)
+#pragma unroll
+                for (int q = 0; q < KR; q++) o[r * KR + q] = acc[r][q];
+        }
+    };
+    // the thread's entries of the sum of the parts (in order)
+    auto gather = [&](cx<T> (&s)[NV]) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NV; u++) {
+            const int v = t + u * nt;
+            if (v < F) {
+#pragma unroll
+                for (int p = 0; p < CS_PARTS; p++)
+                    if (p < parts) s[u] += pr[p * F + v];
+            }
+        }
+    };
+    auto clear = [&](cx<T> (&s)[NV]) {
+#pragma unroll
+        for (int u = 0; u < NV; u++) s[u] = czero<T>();
+    };
+    auto put = [&](cx<T>* f, const cx<T> (&s)[NV], T sgn) {   // f = sgn s, visible to the workgroup
+#pragma unroll
+        for (int u = 0; u < NV; u++)
+            if (t + u * nt < F) f[t + u * nt] = sgn * s[u];
+        __syncthreads();
+    };
+    // s += sum over the slots [s0, 9) of the sites of parity p applied to z (slot 0: the site itself)
+    auto outer = [&](int p, int s0, cx<T> (&s)[NV]) {
+        for (int sa = s0; sa < 9; sa += H) {
+            const int ns = min(H, 9 - sa);
+            // SU entries per thread are loaded before the first is stored
+            constexpr int SU = 4;
+            for (int e0 = t; e0 < ns * F; e0 += SU * nt) {
+                cx<T> v[SU];
+                int to[SU];
+#pragma unroll
+                for (int u = 0; u < SU; u++) {
+                    const int e = e0 + u * nt;
+                    v[u] = czero<T>();
+                    to[u] = -1;
+                    if (e >= ns * F) continue;
+                    int m = e / nd;
+                    const int c = e - m * nd, q = m / (ns * bv);
+                    m -= q * (ns * bv);
+                    const int sl = sa + m / bv, l = m % bv;
+                    to[u] = (m * nd + c) * KR + q;
+                    if ((on >> q) & 1u) {
+                        const int j = !sl ? sidx[p * bv + l] : BIG ? neighbour(p, l, sl - 1) : nbg[(p * 8 + sl - 1) * bv + l];
+                        v[u] = z[(size_t)q * ld + ((size_t)(sl ? 1 - p : p) * g.vh + j) * nd + c];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < SU; u++)
+                    if (to[u] >= 0) sg[to[u]] = v[u];
+            }
+            __syncthreads();
+            product([&](int l) { return op.M + (((size_t)p * g.vh + sidx[p * bv + l]) * 9 + sa) * nn; },
+                    [&](int) { return ns; },
+                    [&](int l, int e, int& slot, int& x0) {
+                        slot = e;
+                        x0 = (int)(sg - so) + (e * bv + l) * nd * KR;
+                    });
+            gather(s);
+            __syncthreads();   // the staged inputs and the partial rows are free again
+        }
+    };
+    // s += [M0 f0 +] sum of the inner hops of parity p applied to the field f
+    auto inner = [&](int p, const cx<T>* f0, const cx<T>* f, cx<T> (&s)[NV]) {
+        const int o0 = f0 ? (int)(f0 - so) : 0, o1 = (int)(f - so), self = f0 ? 1 : 0;
+        product([&](int l) { return op.M + ((size_t)p * g.vh + sidx[p * bv + l]) * 9 * nn; },
+                [&](int l) { return self + cnt[p * bv + l]; },
+                [&](int l, int e, int& slot, int& x0) {
+                    if (e < self) {
+                        slot = 0;
+                        x0 = o0 + l * nd * KR;
+                    } else {
+                        const int w = lst[(p * bv + l) * 8 + e - self];
+                        slot = w & 15;
+                        x0 = o1 + (w >> 4) * nd * KR;
+                    }
+                });
+        gather(s);
+    };
+    // s = Minv_e f
+    auto minv = [&](const cx<T>* f, cx<T> (&s)[NV]) {
+        const int o = (int)(f - so);
+        product([&](int l) { return op.Minv + (size_t)sidx[l] * nn; }, [&](int) { return 1; },
+                [&](int l, int, int& slot, int& x0) {
+                    slot = 0;
+                    x0 = o + l * nd * KR;
+                });
+        clear(s);
+        gather(s);
+    };
+    cx<T> rho[NV], eo[NV], sv[NV];
+    // z_e + t0_e = Minv (b_e - H z)
+    clear(sv);
+    outer(0, 1, sv);
+#pragma unroll
+    for (int u = 0; u < NV; u++)
+        if (t + u * nt < F) sv[u] = (myon ? b[field(0, u)] : czero<T>()) - sv[u];
+    put(se, sv, T(1));
+    minv(se, sv);
+    // stored at once: no other workgroup reads these z, and the odd residual of
+    // this one wants z + t0 at the inner hops
+#pragma unroll
+    for (int u = 0; u < NV; u++)
+        if (myon && t + u * nt < F) z[field(0, u)] = sv[u];
+    __syncthreads();
+    // rho = b_o - M0 z_o - H z - H_int t0
+    clear(rho);
+    outer(1, 0, rho);
+#pragma unroll
+    for (int u = 0; u < NV; u++) {
+        if (t + u * nt < F) rho[u] = (myon ? b[field(1, u)] : czero<T>()) - rho[u];
+        eo[u] = czero<T>();
+    }
+    put(so, rho, T(1));
+    const int lane = t & 63, w = t >> 6, nw = nt >> 6;
+    for (int it = 0; it < mr_steps; it++) {
+        clear(sv);
+        inner(0, nullptr, so, sv);
+        put(se, sv, T(1));
+        minv(se, sv);
+        put(se, sv, T(-1));   // -Minv H rho: the odd pass adds all its terms
+        clear(sv);
+        inner(1, so, se, sv);
+        double d[3] = {0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < NV; u++)
+            if (t + u * nt < F) {
+                const cx<T> p = cmulc(sv[u], rho[u]);
+                d[0] += p.re;
+                d[1] += p.im;
+                d[2] += norm2(sv[u]);
+            }
+        // the lanes of one RHS are KR apart
+#pragma unroll
+        for (int o = 32; o >= KR; o >>= 1)
+#pragma unroll
+            for (int c = 0; c < 3; c++) d[c] += __shfl_xor(d[c], o, 64);
+        if (lane < KR)
+#pragma unroll
+            for (int c = 0; c < 3; c++) red[(w * KR + lane) * 3 + c] = d[c];
+        __syncthreads();
+        double a0 = 0, a1 = 0, a2 = 0;
+        for (int v = 0; v < nw; v++) {
+            const double* rv = red + (v * KR + myq) * 3;
+            a0 += rv[0];
+            a1 += rv[1];
+            a2 += rv[2];
+        }
+        if (a2 > 0) {
+            const cx<T> alpha = {T(a0 / a2), T(a1 / a2)};
+#pragma unroll
+            for (int u = 0; u < NV; u++) {
+                eo[u] += alpha * rho[u];
+                rho[u] -= alpha * sv[u];
+            }
+        }
+        if (it + 1 < mr_steps) put(so, rho, T(1));
+    }
+    put(so, eo, T(1));
+    clear(sv);
+    inner(0, nullptr, so, sv);
+    put(se, sv, T(1));
+    minv(se, sv);
+    if (!myon) return;
+#pragma unroll
+    for (int u = 0; u < NV; u++)
+        if (t + u * nt < F) {
+            z[field(0, u)] -= sv[u];
+            z[field(1, u)] += eo[u];
+        }
+}
+
+// How a block of bv even and bv odd sites is worked on by one workgroup for a
+// group of kr right-hand sides; ok = false where its fields don't fit in LDS
+// or registers.
+struct SapShape {
+    bool ok, big;
+    int nt, nv, parts, hops;
+    size_t lds;
+};
+template <class T>
+static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = false) {
+    SapShape s{};
+    s.big = big;
+    const int lc = nd / rpl, f = bv * nd * kr;
+    const size_t unit = sizeof(cx<T>) * f;
+    const size_t fixed = sizeof(cx<T>) * 2 * kr + sizeof(double) * 3 * kr * (CS_NT / 64) + (size_t)(big ? 48 : 112) * bv;
+    const long units = (long)((CS_LDS - fixed) / unit) - 2;
+    if (units < 2) return s;
+    // parts: the fewest rounds of the lane groups per column, with at most
+    // CS_PARTS partial rows to add and LDS left for a staged hop
+    double best = 0;
+    for (int p = 1; p <= CS_PARTS && p < units && p <= nd; p++) {
+        const double cost = (double)((bv * p + CS_NT / lc - 1) / (CS_NT / lc)) / p;
+        if (p == 1 || cost < best - 1e-9) { best = cost; s.parts = p; }
+    }
+    const int work = std::max(std::min(bv * s.parts * lc, CS_NT), (f + 2) / 3);
+    s.nt = std::min(CS_NT, (work + 63) / 64 * 64);
+    s.nv = (f + s.nt - 1) / s.nt;
+    // the nine slots of the residual in one round, or in two, three, five
+    const long left = units - s.parts;
+    s.hops = left >= 9 ? 9 : left >= 5 ? 5 : left >= 3 ? 3 : left >= 2 ? 2 : 1;
+    s.lds = unit * (2 + s.parts + s.hops) + fixed;
+    s.ok = s.nv <= 3 && lc <= CS_NT;
     return s;
 }
 
-// One right-hand side per workgroup (grid.y = RHS).
-// NTMAX: the workgroup size the kernel is compiled for (wider batches of
-// loads where fewer threads leave more registers per thread)
-template <class T, class S, int NTMAX>
-__global__ void __launch_bounds__(NTMAX) k_coarse_sap1(CoarseOp<T, S> op, const int* __restrict__ blocks, const cx<T>* __restrict__ b,
-                             cx<T>* __restrict__ z, int mr_steps, long ld, Mask mk) {
-    if (!mk.on(blockIdx.y)) return;
-    b += blockIdx.y * ld;
-    z += blockIdx.y * ld;
-    extern __shared__ char smem_raw[];
-    const Geom g = op.g;
-    const int nd = op.nd, bvh = g.bvh;
-    const size_t nn = (size_t)nd * nd;
-    constexpr int RB = NTMAX <= 512 ? 20 : 8;
-    cx<T>* so = reinterpret_cast<cx<T>*>(smem_raw);  // [bvh][nd] odd-site field
-    cx<T>* se = so + bvh * nd;                        // even-site field
-    cx<T>* tm = se + bvh * nd;                        // temporary (even)
-    double* red = reinterpret_cast<double*>(tm + bvh * nd);
-    const int blk = blocks[blockIdx.x];
-    const int base = blk << g.lbvh;
-    const int t = threadIdx.x;
-    const bool act = t < bvh * nd;
-    const int l = act ? t / nd : 0, r = act ? t % nd : 0;
-    const int i = base + l;
-    int xe[4], xo[4], nbe[8], nbo[8];
-    cb_coords(g, 0, i, xe);
-    cb_coords(g, 1, i, xo);
-    for (int k = 0; k < 8; k++) {
-        int y[4];
-        nb_coords(g, xe, k, y);
-        nbe[k] = cb_index(g, y);
-        nb_coords(g, xo, k, y);
-        nbo[k] = cb_index(g, y);
+template <class T, class S, int KR, int RPL, int NV, bool BIG = false>
+static void coarse_sap_go(const CoarseOp<T, S>& op, const int* blocks, int nblocks, SapTab tab, int bv, const cx<T>* b,
+                          cx<T>* z, int mr_steps, hipStream_t s, int nr, long ld, Mask mk, const SapShape& sh) {
+    static std::mutex mu;
+    static size_t configured = 65536;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        // a refusal leaves its error for the launch below to report
+        if (sh.lds > configured && hipFuncSetAttribute((const void*)k_coarse_sap<T, S, KR, RPL, NV, BIG>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds) == hipSuccess)
+            configured = sh.lds;
     }
-    const size_t ge = i, go = (size_t)g.vh + i;
-    auto hop_glob = [&](size_t gs, int p, const int* nbj, const cx<T>* v) {
-        cx<T> h = czero<T>();
-        for (int k = 0; k < 8; k++) {
-            size_t gy = (size_t)(1 - p) * g.vh + nbj[k];
-            h += row_apply<T, S, RB>(op.M + (gs * 9 + 1 + k) * nn, nd, r, v + gy * nd);
-        }
-        return h;
-    };
-    auto hop_int = [&](size_t gs, const int* nbj, const cx<T>* buf) {
-        cx<T> h = czero<T>();
-        for (int k = 0; k < 8; k++) {
-            if ((nbj[k] >> g.lbvh) != blk) continue;
-            h += row_apply<T, S, RB>(op.M + (gs * 9 + 1 + k) * nn, nd, r, buf + (nbj[k] - base) * nd);
-        }
-        return h;
-    };
-    // t0_e = Minv (b_e - H z) - z_e
-    cx<T> t0 = czero<T>(), rho = czero<T>(), eo = czero<T>(), sv = czero<T>();
-    if (act) tm[l * nd + r] = b[ge * nd + r] - hop_glob(ge, 0, nbe, z);
-    __syncthreads();
-    if (act) {
-        t0 = row_apply<T, S, RB>(op.Minv + ge * nn, nd, r, tm + l * nd) - z[ge * nd + r];
-        se[l * nd + r] = t0;
-        so[l * nd + r] = z[go * nd + r];
-    }
-    __syncthreads();
-    // f_o = b_o - M0 z_o - H z - H_int t0
-    if (act) rho = b[go * nd + r] - row_apply<T, S, RB>(op.M + go * 9 * nn, nd, r, so + l * nd) - hop_glob(go, 1, nbo, z) - hop_int(go, nbo, se);
-    __syncthreads();
-    if (act) so[l * nd + r] = rho;
-    __syncthreads();
-    const int lane = t & 63, w = t >> 6, nw = (blockDim.x + 63) >> 6;
-    for (int it = 0; it < mr_steps; it++) {
-        if (act) tm[l * nd + r] = hop_int(ge, nbe, so);
-        __syncthreads();
-        cx<T> tv = czero<T>();
-        if (act) tv = row_apply<T, S, RB>(op.Minv + ge * nn, nd, r, tm + l * nd);
-        __syncthreads();
-        if (act) se[l * nd + r] = tv;
-        __syncthreads();
-        double sr = 0, si = 0, ss = 0;
-        if (act) {
-            sv = row_apply<T, S, RB>(op.M + go * 9 * nn, nd, r, so + l * nd) - hop_int(go, nbo, se);
-            cx<T> d = cmulc(sv, rho);
-            sr = d.re; si = d.im; ss = norm2(sv);
-        }
-        sr = wave_sum(sr); si = wave_sum(si); ss = wave_sum(ss);
-        if (lane == 0) { red[3 * w] = sr; red[3 * w + 1] = si; red[3 * w + 2] = ss; }
-        __syncthreads();
-        sr = si = ss = 0;
-        for (int q = 0; q < nw; q++) { sr += red[3 * q]; si += red[3 * q + 1]; ss += red[3 * q + 2]; }
-        if (ss > 0 && act) {
-            cx<T> alpha = {T(sr / ss), T(si / ss)};
-            eo += alpha * rho;
-            rho -= alpha * sv;
-        }
-        __syncthreads();
-        if (act) so[l * nd + r] = (it + 1 < mr_steps) ? rho : eo;
-        __syncthreads();
-    }
-    if (mr_steps == 0) {
-        if (act) so[l * nd + r] = eo;
-        __syncthreads();
-    }
-    if (act) tm[l * nd + r] = hop_int(ge, nbe, so);
-    __syncthreads();
-    if (act) {
-        cx<T> ee = t0 - row_apply<T, S, RB>(op.Minv + ge * nn, nd, r, tm + l * nd);
-        z[ge * nd + r] += ee;
-        z[go * nd + r] += eo;
-    }
+    dim3 grid(nblocks, (nr + KR - 1) / KR);
+    k_coarse_sap<T, S, KR, RPL, NV, BIG><<<grid, sh.nt, sh.lds, s>>>(op, blocks, tab, bv, b, z, mr_steps, ld, nr, mk, sh.parts,
+                                                               sh.hops);
 }
 
-// Coarse SAP half sweep on SAP blocks that are not the level's layout blocks
-// (any extents with two colours, e.g. 2 x 3^3 on a 12 x 6^3 level): the block's
-// sites come from tables (SapTab).  One workgroup per (block, RHS); thread
-// (site l, row group rr) holds NR rows rr + q nd/NR of the even site l and the
-// odd site l of the block (NR = 2 when bv * nd exceeds a workgroup).  Same
-// algebra and summation order as k_coarse_sap1.
-template <class T, class S, int NTMAX, int NR>
-__global__ void __launch_bounds__(NTMAX) k_coarse_sap_t(CoarseOp<T, S> op, const int* __restrict__ blocks, SapTab tab,
-                                                        const cx<T>* __restrict__ b, cx<T>* __restrict__ z,
-                                                        int mr_steps, long ld, Mask mk) {
-    if (!mk.on(blockIdx.y)) return;
-    b += blockIdx.y * ld;
-    z += blockIdx.y * ld;
-    extern __shared__ char smem_raw[];
-    const Geom g = op.g;
-    const int nd = op.nd, bv = tab.bv, ndr = nd / NR;
-    const size_t nn = (size_t)nd * nd;
-    constexpr int RB = 8;
-    cx<T>* so = reinterpret_cast<cx<T>*>(smem_raw);  // [bv][nd] odd-site field
-    cx<T>* se = so + bv * nd;                         // even-site field
-    cx<T>* tm = se + bv * nd;                         // temporary (even)
-    double* red = reinterpret_cast<double*>(tm + bv * nd);
-    const int blk = blocks[blockIdx.x];
-    const int t = threadIdx.x;
-    const bool act = t < bv * ndr;
-    const int l = act ? t / ndr : 0, rr = act ? t % ndr : 0;
-    const int ie = tab.sites[((size_t)blk * 2 + 0) * bv + l];
-    const int io = tab.sites[((size_t)blk * 2 + 1) * bv + l];
-    int xe[4], xo[4], nbe[8], nbo[8], lce[8], lco[8];
-    cb_coords(g, 0, ie, xe);
-    cb_coords(g, 1, io, xo);
-    for (int k = 0; k < 8; k++) {
-        int y[4];
-        nb_coords(g, xe, k, y);
-        nbe[k] = cb_index(g, y);
-        size_t gy = (size_t)g.vh + nbe[k];
-        lce[k] = (tab.of[gy] == blk) ? tab.loc[gy] : -1;
-        nb_coords(g, xo, k, y);
-        nbo[k] = cb_index(g, y);
-        gy = (size_t)nbo[k];
-        lco[k] = (tab.of[gy] == blk) ? tab.loc[gy] : -1;
-    }
-    const size_t ge = ie, go = (size_t)g.vh + io;
-    auto hop_glob = [&](size_t gs, int p, const int* nbj, const cx<T>* v, int r) {
-        cx<T> h = czero<T>();
-        for (int k = 0; k < 8; k++) {
-            size_t gy = (size_t)(1 - p) * g.vh + nbj[k];
-            h += row_apply<T, S, RB>(op.M + (gs * 9 + 1 + k) * nn, nd, r, v + gy * nd);
-        }
-        return h;
+template <class T, class S, int RPL>
+static void coarse_sap_pick(const CoarseOp<T, S>& op, const int* blocks, int nblocks, SapTab tab, const cx<T>* b, cx<T>* z,
+                            int mr_steps, hipStream_t s, int nr, long ld, Mask mk) {
+    const int bv = tab.bv ? tab.bv : op.g.bvh;
+    auto launch = [&](auto kr, const SapShape& sh) {
+        constexpr int KR = decltype(kr)::value;
+        if (sh.nv == 1) coarse_sap_go<T, S, KR, RPL, 1>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
+        else if (sh.nv == 2) coarse_sap_go<T, S, KR, RPL, 2>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
+        else coarse_sap_go<T, S, KR, RPL, 3>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
     };
-    auto hop_int = [&](size_t gs, const int* lcj, const cx<T>* buf, int r) {
-        cx<T> h = czero<T>();
-        for (int k = 0; k < 8; k++) {
-            if (lcj[k] < 0) continue;
-            h += row_apply<T, S, RB>(op.M + (gs * 9 + 1 + k) * nn, nd, r, buf + lcj[k] * nd);
-        }
-        return h;
-    };
-    cx<T> t0[NR], rho[NR], eo[NR], sv[NR];
-#pragma unroll
-    for (int q = 0; q < NR; q++) t0[q] = rho[q] = eo[q] = sv[q] = czero<T>();
-    // t0_e = Minv (b_e - H z) - z_e
-    if (act)
-#pragma unroll
-        for (int q = 0; q < NR; q++) {
-            const int r = rr + q * ndr;
-            tm[l * nd + r] = b[ge * nd + r] - hop_glob(ge, 0, nbe, z, r);
-        }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int q = 0; q < NR; q++) {
-            const int r = rr + q * ndr;
-            t0[q] = row_apply<T, S, RB>(op.Minv + ge * nn, nd, r, tm + l * nd) - z[ge * nd + r];
-            se[l * nd + r] = t0[q];
-            so[l * nd + r] = z[go * nd + r];
-        }
-    __syncthreads();
-    // f_o = b_o - M0 z_o - H z - H_int t0
-    if (act)
-#pragma unroll
-        for (int q = 0; q < NR; q++) {
-            const int r = rr + q * ndr;
-            rho[q] = b[go * nd + r] - row_apply<T, S, RB>(op.M + go * 9 * nn, nd, r, so + l * nd) -
-                     hop_glob(go, 1, nbo, z, r) - hop_int(go, lco, se, r);
-        }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int q = 0; q < NR; q++) so[l * nd + rr + q * ndr] = rho[q];
-    __syncthreads();
-    const int lane = t & 63, w = t >> 6, nw = (blockDim.x + 63) >> 6;
-    for (int it = 0; it < mr_steps; it++) {
-        if (act)
-#pragma unroll
-            for (int q = 0; q < NR; q++) {
-                const int r = rr + q * ndr;
-                tm[l * nd + r] = hop_int(ge, lce, so, r);
-            }
-        __syncthreads();
-        cx<T> tv[NR];
-#pragma unroll
-        for (int q = 0; q < NR; q++) tv[q] = czero<T>();
-        if (act)
-#pragma unroll
-            for (int q = 0; q < NR; q++) tv[q] = row_apply<T, S, RB>(op.Minv + ge * nn, nd, rr + q * ndr, tm + l * nd);
-        __syncthreads();
-        if (act)
-#pragma unroll
-            for (int q = 0; q < NR; q++) se[l * nd + rr + q * ndr] = tv[q];
-        __syncthreads();
-        double sr = 0, si = 0, ss = 0;
-        if (act)
-#pragma unroll
-            for (int q = 0; q < NR; q++) {
-                const int r = rr + q * ndr;
-                sv[q] = row_apply<T, S, RB>(op.M + go * 9 * nn, nd, r, so + l * nd) - hop_int(go, lco, se, r);
-                cx<T> d = cmulc(sv[q], rho[q]);
-                sr += d.re; si += d.im; ss += norm2(sv[q]);
-            }
-        sr = wave_sum(sr); si = wave_sum(si); ss = wave_sum(ss);
-        if (lane == 0) { red[3 * w] = sr; red[3 * w + 1] = si; red[3 * w + 2] = ss; }
-        __syncthreads();
-        sr = si = ss = 0;
-        for (int v = 0; v < nw; v++) { sr += red[3 * v]; si += red[3 * v + 1]; ss += red[3 * v + 2]; }
-        if (ss > 0 && act) {
-            cx<T> alpha = {T(sr / ss), T(si / ss)};
-#pragma unroll
-            for (int q = 0; q < NR; q++) {
-                eo[q] += alpha * rho[q];
-                rho[q] -= alpha * sv[q];
-            }
-        }
-        __syncthreads();
-        if (act)
-#pragma unroll
-            for (int q = 0; q < NR; q++) so[l * nd + rr + q * ndr] = (it + 1 < mr_steps) ? rho[q] : eo[q];
-        __syncthreads();
+    // the widest group of right-hand sides that fits, shares a block's loads and
+    // still gives the launch about one workgroup for every second CU (24 blocks of
+    // 2x3^3 and 4 RHS: 397 us as 96 workgroups of one RHS, 506 us as 48 of two)
+    auto want = [&](int kr) { return nr > kr / 2 && nblocks * ((nr + kr - 1) / kr) >= 128; };
+    if constexpr (sizeof(T) == 4 && (sizeof(S) != 2 || RPL == 4)) {
+        const SapShape s4 = coarse_sap_shape<T>(bv, op.nd, 4, RPL);
+        if (s4.ok && s4.parts + s4.hops >= 6 && want(4)) return launch(std::integral_constant<int, 4>{}, s4);
     }
-    if (mr_steps == 0) {
-        if (act)
-#pragma unroll
-            for (int q = 0; q < NR; q++) so[l * nd + rr + q * ndr] = eo[q];
-        __syncthreads();
+    if constexpr (sizeof(S) != 2 || RPL == 4) {
+        const SapShape s2 = coarse_sap_shape<T>(bv, op.nd, 2, RPL);
+        if (s2.ok && s2.parts + s2.hops >= 4 && want(2)) return launch(std::integral_constant<int, 2>{}, s2);
     }
-    if (act)
-#pragma unroll
-        for (int q = 0; q < NR; q++) {
-            const int r = rr + q * ndr;
-            tm[l * nd + r] = hop_int(ge, lce, so, r);
-        }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int q = 0; q < NR; q++) {
-            const int r = rr + q * ndr;
-            cx<T> ee = t0[q] - row_apply<T, S, RB>(op.Minv + ge * nn, nd, r, tm + l * nd);
-            z[ge * nd + r] += ee;
-            z[go * nd + r] += eo[q];
-        }
+    const SapShape s1 = coarse_sap_shape<T>(bv, op.nd, 1, RPL);
+    if (s1.ok) return launch(std::integral_constant<int, 1>{}, s1);
+    const SapShape sb = coarse_sap_shape<T>(bv, op.nd, 1, RPL, true);
+    if (!sb.ok) throw std::invalid_argument("coarse SAP block too large for one workgroup");
+    coarse_sap_go<T, S, 1, RPL, 3, true>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sb);
 }
 
-// KR right-hand sides at once: every block entry loaded is applied to the KR
-// vectors v + vo[q] (q < KR), accumulated into s[q] in the same column order
-// as row_apply (so a RHS gets the same sums alone and in a group)
-template <class T, class S, int KR, int RA_BATCH>
-__device__ __forceinline__ void row_apply_k(const cx<S>* __restrict__ A, int nd, int r, const cx<T>* v,
-                                            const size_t (&vo)[KR], cx<T> (&s)[KR]) {
-    using W = cx_word<S>;
-    const W* Aw = reinterpret_cast<const W*>(A);
-#pragma unroll
-    for (int q = 0; q < KR; q++) s[q] = czero<T>();
-    for (int c0 = 0; c0 < nd; c0 += RA_BATCH) {
-        W a[RA_BATCH];
-#pragma unroll
-        for (int u = 0; u < RA_BATCH; u++) a[u] = (c0 + u < nd) ? Aw[(size_t)(c0 + u) * nd + r] : W{};
-#pragma unroll
-        for (int q = 0; q < KR; q++) {
-            cx<T> x[RA_BATCH];
-#pragma unroll
-            for (int u = 0; u < RA_BATCH; u++) x[u] = (c0 + u < nd) ? v[vo[q] + c0 + u] : czero<T>();
-#pragma unroll
-            for (int u = 0; u < RA_BATCH; u++)
-                if (c0 + u < nd) s[q] += ccast<T>(__builtin_bit_cast(cx<S>, a[u])) * x[u];
-        }
-    }
-}
-
-// Coarse SAP half sweep for KR right-hand sides per workgroup: workgroup =
-// (block, group of KR RHS), thread = (local site l, row r) for both parities;
-// each block entry is loaded once per use for the whole group.  The fields of
-// the group live in LDS as [q][bvh][nd].  Right-hand sides beyond nr or masked
-// off take no part (their z is not touched).  NTMAX: the workgroup size the
-// kernel is compiled for (wider batches of loads where fewer threads leave
-// more registers per thread).
-// Registers: the single-precision group of four is held to 128 VGPRs (four
-// waves per SIMD, three workgroups of the 2^4 blocks per CU): t0 and e_o live
-// in LDS and the column batches are shorter.  Latency, not bandwidth, bounds
-// this kernel, and one workgroup per CU left most of the wait exposed.
-template <class T, class S, int NTMAX, int KR>
-__global__ void __launch_bounds__(NTMAX, (KR >= 4 && sizeof(T) == 4) ? 4 : 1) k_coarse_sap(CoarseOp<T, S> op, const int* __restrict__ blocks, const cx<T>* __restrict__ b,
-                             cx<T>* __restrict__ z, int mr_steps, long ld, int nr, Mask mk) {
-    const int q0 = blockIdx.y * KR;
-    bool on[KR];
-    bool any = false;
-    size_t go_[KR], lo_[KR];   // offsets of member q in the global vector sets and in the LDS fields
-#pragma unroll
-    for (int q = 0; q < KR; q++) {
-        on[q] = (q0 + q < nr) && mk.on(q0 + q);
-        any |= on[q];
-        // members past the batch read the first member's data (never written)
-        go_[q] = (size_t)((q0 + q < nr) ? q : 0) * ld;
-    }
-    if (!any) return;
-    b += (size_t)q0 * ld;
-    z += (size_t)q0 * ld;
-    extern __shared__ char smem_raw[];
-    const Geom g = op.g;
-    const int nd = op.nd, bvh = g.bvh;
-    const size_t nn = (size_t)nd * nd;
-    const size_t fs = (size_t)bvh * nd;               // one field of the block
-#pragma unroll
-    for (int q = 0; q < KR; q++) lo_[q] = q * fs;
-    constexpr int RB = sizeof(T) == 8 ? (NTMAX <= 512 ? 4 : 2) : (NTMAX <= 512 && KR < 4 ? 10 : 5);
-    cx<T>* so = reinterpret_cast<cx<T>*>(smem_raw);  // [KR][bvh][nd] odd-site fields
-    cx<T>* se = so + KR * fs;                         // even-site fields
-    cx<T>* tm = se + KR * fs;                         // temporaries (even)
-    cx<T>* st = tm + KR * fs;                         // t0 (even), kept for the final update
-    cx<T>* seo = st + KR * fs;                        // the odd-site correction e_o
-    const int nw = (blockDim.x + 63) >> 6;
-    double* red = reinterpret_cast<double*>(seo + KR * fs);  // [KR][nw][3]
-    int* nbl = reinterpret_cast<int*>(red + 3 * KR * nw);   // [2][8][bvh] neighbour indices
-    const int blk = blocks[blockIdx.x];
-    const int base = blk << g.lbvh;
-    const int t = threadIdx.x;
-    const bool act = t < bvh * nd;
-    const int l = act ? t / nd : 0, r = act ? t % nd : 0;
-    const int i = base + l;
-    if (act && r == 0) {
-        int xe[4], xo[4];
-        cb_coords(g, 0, i, xe);
-        cb_coords(g, 1, i, xo);
-        for (int k = 0; k < 8; k++) {
-            int y[4];
-            nb_coords(g, xe, k, y);
-            nbl[k * bvh + l] = cb_index(g, y);
-            nb_coords(g, xo, k, y);
-            nbl[(8 + k) * bvh + l] = cb_index(g, y);
-        }
-    }
-    // the neighbour indices of even (odd) sites: nbe[k * bvh] (nbo[k * bvh])
-    const int* nbe = nbl + l;
-    const int* nbo = nbl + 8 * bvh + l;
-    __syncthreads();
-    const size_t ge = i, go = (size_t)g.vh + i;
-    // sum over the 8 hops of site gs (parity p) applied to the global vectors
-    auto hop_glob = [&](size_t gs, int p, const int* nbj, cx<T> (&h)[KR]) {
-#pragma unroll
-        for (int q = 0; q < KR; q++) h[q] = czero<T>();
-#pragma unroll 1
-        for (int k = 0; k < 8; k++) {
-            size_t gy = (size_t)(1 - p) * g.vh + nbj[k * bvh];
-            cx<T> u[KR];
-            row_apply_k<T, S, KR, RB>(op.M + (gs * 9 + 1 + k) * nn, nd, r, z + gy * nd, go_, u);
-#pragma unroll
-            for (int q = 0; q < KR; q++) h[q] += u[q];
-        }
-    };
-    // sum over the hops that stay inside the block, applied to LDS fields
-    auto hop_int = [&](size_t gs, const int* nbj, const cx<T>* buf, cx<T> (&h)[KR]) {
-#pragma unroll
-        for (int q = 0; q < KR; q++) h[q] = czero<T>();
-#pragma unroll 1
-        for (int k = 0; k < 8; k++) {
-            const int j = nbj[k * bvh];
-            if ((j >> g.lbvh) != blk) continue;
-            cx<T> u[KR];
-            row_apply_k<T, S, KR, RB>(op.M + (gs * 9 + 1 + k) * nn, nd, r, buf + (j - base) * nd, lo_, u);
-#pragma unroll
-            for (int q = 0; q < KR; q++) h[q] += u[q];
-        }
-    };
-    const int me = l * nd + r;
-    cx<T> rho[KR], sv[KR], h[KR], u[KR];
-#pragma unroll
-    for (int q = 0; q < KR; q++) {
-        rho[q] = sv[q] = czero<T>();
-        if (act) seo[q * fs + me] = czero<T>();
-    }
-    // t0_e = Minv (b_e - H z) - z_e
-    if (act) {
-        hop_glob(ge, 0, nbe, h);
-#pragma unroll
-        for (int q = 0; q < KR; q++) tm[q * fs + me] = b[go_[q] + ge * nd + r] - h[q];
-    }
-    __syncthreads();
-    if (act) {
-        row_apply_k<T, S, KR, RB>(op.Minv + ge * nn, nd, r, tm + l * nd, lo_, u);
-#pragma unroll
-        for (int q = 0; q < KR; q++) {
-            const cx<T> t0 = u[q] - z[go_[q] + ge * nd + r];
-            se[q * fs + me] = t0;
-            st[q * fs + me] = t0;
-            so[q * fs + me] = z[go_[q] + go * nd + r];
-        }
-    }
-    __syncthreads();
-    // f_o = b_o - M0 z_o - H z - H_int t0
-    if (act) {
-        cx<T> hg[KR], hi[KR];
-        row_apply_k<T, S, KR, RB>(op.M + go * 9 * nn, nd, r, so + l * nd, lo_, u);
-        hop_glob(go, 1, nbo, hg);
-        hop_int(go, nbo, se, hi);
-#pragma unroll
-        for (int q = 0; q < KR; q++) rho[q] = b[go_[q] + go * nd + r] - u[q] - hg[q] - hi[q];
-    }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int q = 0; q < KR; q++) so[q * fs + me] = rho[q];
-    __syncthreads();
-    const int lane = t & 63, w = t >> 6;
-    for (int it = 0; it < mr_steps; it++) {
-        if (act) {
-            hop_int(ge, nbe, so, h);
-#pragma unroll
-            for (int q = 0; q < KR; q++) tm[q * fs + me] = h[q];
-        }
-        __syncthreads();
-        if (act) row_apply_k<T, S, KR, RB>(op.Minv + ge * nn, nd, r, tm + l * nd, lo_, u);
-        __syncthreads();
-        if (act)
-#pragma unroll
-            for (int q = 0; q < KR; q++) se[q * fs + me] = u[q];
-        __syncthreads();
-        double sr[KR], si[KR], ss[KR];
-        if (act) {
-            row_apply_k<T, S, KR, RB>(op.M + go * 9 * nn, nd, r, so + l * nd, lo_, u);
-            hop_int(go, nbo, se, h);
-        }
-#pragma unroll
-        for (int q = 0; q < KR; q++) {
-            sr[q] = si[q] = ss[q] = 0;
-            if (act) {
-                sv[q] = u[q] - h[q];
-                cx<T> d = cmulc(sv[q], rho[q]);
-                sr[q] = d.re; si[q] = d.im; ss[q] = norm2(sv[q]);
-            }
-            sr[q] = wave_sum(sr[q]); si[q] = wave_sum(si[q]); ss[q] = wave_sum(ss[q]);
-            if (lane == 0) { red[(q * nw + w) * 3] = sr[q]; red[(q * nw + w) * 3 + 1] = si[q]; red[(q * nw + w) * 3 + 2] = ss[q]; }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < KR; q++) {
-            double a0 = 0, a1 = 0, a2 = 0;
-            for (int v = 0; v < nw; v++) { a0 += red[(q * nw + v) * 3]; a1 += red[(q * nw + v) * 3 + 1]; a2 += red[(q * nw + v) * 3 + 2]; }
-            if (a2 > 0 && act) {
-                cx<T> alpha = {T(a0 / a2), T(a1 / a2)};
-                seo[q * fs + me] += alpha * rho[q];
-                rho[q] -= alpha * sv[q];
-            }
-        }
-        __syncthreads();
-        if (act)
-#pragma unroll
-            for (int q = 0; q < KR; q++) so[q * fs + me] = (it + 1 < mr_steps) ? rho[q] : seo[q * fs + me];
-        __syncthreads();
-    }
-    if (mr_steps == 0) {
-        if (act)
-#pragma unroll
-            for (int q = 0; q < KR; q++) so[q * fs + me] = seo[q * fs + me];
-        __syncthreads();
-    }
-    if (act) {
-        hop_int(ge, nbe, so, h);
-#pragma unroll
-        for (int q = 0; q < KR; q++) tm[q * fs + me] = h[q];
-    }
-    __syncthreads();
-    if (act) {
-        row_apply_k<T, S, KR, RB>(op.Minv + ge * nn, nd, r, tm + l * nd, lo_, u);
-#pragma unroll
-        for (int q = 0; q < KR; q++) {
-            if (!on[q]) continue;
-            z[q * ld + ge * nd + r] += st[q * fs + me] - u[q];
-            z[q * ld + go * nd + r] += seo[q * fs + me];
-        }
-    }
-}
-
-// LDS of one member of a multi-RHS group: five block fields (odd sites, even
-// sites, a temporary, t0, e_o) and the partial sums of three reductions per
-// wave
-template <class T>
-static size_t coarse_sap_member_lds(int bvh, int nd) {
-    const int nw = (bvh * nd + 63) / 64;
-    return 5 * sizeof(cx<T>) * bvh * nd + 3 * sizeof(double) * nw;
-}
-
-template <class T, class S, int KR>
-static void coarse_sap_launch(const CoarseOp<T, S>& op, const int* blocks, int nblocks, const cx<T>* b, cx<T>* z,
-                              int mr_steps, hipStream_t s, int nr, long ld, Mask mk) {
-    const int nt = ((op.g.bvh * op.nd + 63) / 64) * 64;
-    if constexpr (KR == 1) {
-        const size_t lds = 3 * sizeof(cx<T>) * op.g.bvh * op.nd + 3 * sizeof(double) * (nt / 64);
-        dim3 grid(nblocks, nr);
-        if (nt <= 512) k_coarse_sap1<T, S, 512><<<grid, nt, lds, s>>>(op, blocks, b, z, mr_steps, ld, mk);
-        else k_coarse_sap1<T, S, 1024><<<grid, nt, lds, s>>>(op, blocks, b, z, mr_steps, ld, mk);
-    } else {
-        const size_t lds = coarse_sap_member_lds<T>(op.g.bvh, op.nd) * KR + 16 * sizeof(int) * op.g.bvh;
-        dim3 grid(nblocks, (nr + KR - 1) / KR);
-        if (nt <= 512) k_coarse_sap<T, S, 512, KR><<<grid, nt, lds, s>>>(op, blocks, b, z, mr_steps, ld, nr, mk);
-        else k_coarse_sap<T, S, 1024, KR><<<grid, nt, lds, s>>>(op, blocks, b, z, mr_steps, ld, nr, mk);
-    }
-}
-
-// Right-hand sides are taken in groups of four (two for a batch of two), so a
-// block entry read from memory serves the whole group; a single RHS runs the
-// one-RHS kernel.  Both compute the same sums in the same order.
 template <class T, class S>
 void coarse_sap_half(const CoarseOp<T, S>& op, const int* blocks, int nblocks, const cx<T>* b, cx<T>* z, int mr_steps,
                      hipStream_t s, int nr, long ld, Mask mk, SapTab tab) {
     if (nblocks <= 0) return;
-    if (tab.bv > 0) {
-        // SAP blocks from tables: one workgroup per (block, RHS)
-        const int NR = (tab.bv * op.nd > 1024) ? 2 : 1;
-        const int nt = ((tab.bv * op.nd / NR + 63) / 64) * 64;
-        const size_t lds = 3 * sizeof(cx<T>) * tab.bv * op.nd + 3 * sizeof(double) * (nt / 64);
-        dim3 grid(nblocks, nr);
-        if (NR == 1) k_coarse_sap_t<T, S, 1024, 1><<<grid, nt, lds, s>>>(op, blocks, tab, b, z, mr_steps, ld, mk);
-        else k_coarse_sap_t<T, S, 1024, 2><<<grid, nt, lds, s>>>(op, blocks, tab, b, z, mr_steps, ld, mk);
-        return;
-    }
-    // LDS of a group: five block fields per member and the neighbour table
-    // (kept within the 64 KB a workgroup gets without an opt-in)
-    const size_t member = coarse_sap_member_lds<T>(op.g.bvh, op.nd), nbt = 16 * sizeof(int) * op.g.bvh;
-    if (nr >= 3 && 4 * member + nbt <= 65536) coarse_sap_launch<T, S, 4>(op, blocks, nblocks, b, z, mr_steps, s, nr, ld, mk);
-    else if (nr >= 2 && 2 * member + nbt <= 65536) coarse_sap_launch<T, S, 2>(op, blocks, nblocks, b, z, mr_steps, s, nr, ld, mk);
-    else coarse_sap_launch<T, S, 1>(op, blocks, nblocks, b, z, mr_steps, s, nr, ld, mk);
+    // rows per lane: 16 bytes of a column (nd is even; FP16 columns of an odd N
+    // start on 8-byte boundaries only)
+    if constexpr (sizeof(S) == 8) coarse_sap_pick<T, S, 1>(op, blocks, nblocks, tab, b, z, mr_steps, s, nr, ld, mk);
+    else if constexpr (sizeof(S) == 4) coarse_sap_pick<T, S, 2>(op, blocks, nblocks, tab, b, z, mr_steps, s, nr, ld, mk);
+    else if (op.nd % 4 == 0) coarse_sap_pick<T, S, 4>(op, blocks, nblocks, tab, b, z, mr_steps, s, nr, ld, mk);
+    else coarse_sap_pick<T, S, 2>(op, blocks, nblocks, tab, b, z, mr_steps, s, nr, ld, mk);
 }
 
 // ---------------------------------------------------------------------------
