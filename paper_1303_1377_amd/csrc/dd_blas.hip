@@ -5,7 +5,7 @@
 // storage precision; partial sums are combined in a fixed order.
 #include <algorithm>
 
-#include "dd_kernels.h"
+#include "dd_gmres.h"
 
 namespace dd {
 
@@ -150,56 +150,34 @@ __global__ void __launch_bounds__(RED_NT) k_final_sum(int nc, int m, const cx<do
     if (threadIdx.x == 0) out[(size_t)r * ostride + i] = cx<double>{re, im};
 }
 
-// w -= sum_i h_i V_i ; npart[r*nc + c] = chunk c of ||w||^2.  With hpart != 0
-// the inner products are first summed from the multidot partials.
-//
-// With ga.st (the coarsest GMRES) the stored basis vectors may carry factors
-// sc_i (V_i = sc_i * stored): the partial sums are of the stored vectors, so
-// h_i = sc_i * sum and w -= sum_i (h_i sc_i) stored_i.  The last workgroup of
-// each RHS to finish (atomic count in ga.done, reset by it) then adds the norm
-// partials and folds the column into the state (and scales w when
-// ga.normalize): the norm sum and the Givens update need no launch of their own.
-struct GivensArgs {
-    GmDev* st = nullptr;
-    int j = 0;
-    int* done = nullptr;
-    int normalize = 0;
-};
-__device__ double gm_column_wg(GmDev* st, int j, const cx<double>* h, double hn2, bool normalize);
+// we - sum_{i < m} h_i V_i[e], basis entries loaded in batches so that many
+// loads are in flight (short coarse vectors leave one element per thread:
+// latency bound)
+template <class T>
+__device__ __forceinline__ cx<T> project_out(cx<T> we, const cx<T>* __restrict__ V, long ldv, const cx<T>* hh, int m) {
+    for (int i0 = 0; i0 < m; i0 += UN_BATCH) {
+        cx<T> vv[UN_BATCH];
+#pragma unroll
+        for (int u = 0; u < UN_BATCH; u++) vv[u] = (i0 + u < m) ? V[(size_t)(i0 + u) * ldv] : czero<T>();
+#pragma unroll
+        for (int u = 0; u < UN_BATCH; u++)
+            if (i0 + u < m) we -= hh[i0 + u] * vv[u];
+    }
+    return we;
+}
 
+// w -= sum_i h_i V_i ; npart[r*nc + c] = chunk c of ||w||^2
 template <class T>
 __global__ void __launch_bounds__(RED_NT) k_update_norm(long n, long chunk, int nc, int m, const cx<T>* __restrict__ V,
                                                         long ldv, const cx<double>* __restrict__ h, int hstride,
-                                                        const cx<double>* __restrict__ hpart, cx<double>* hout,
                                                         cx<T>* __restrict__ w, cx<double>* __restrict__ npart, long ldr,
-                                                        long ldw, Mask mk, GivensArgs ga, const double* __restrict__ g,
-                                                        int gstride, cx<float>* __restrict__ wc, long ldc) {
+                                                        long ldw, Mask mk, const double* __restrict__ g, int gstride,
+                                                        cx<float>* __restrict__ wc, long ldc) {
     const int c = blockIdx.x, r = blockIdx.y;
     if (!mk.on(r)) return;
-    const double* scv = ga.st ? ga.st[r].sc : nullptr;
     __shared__ double sh[RED_NT / 64];
     __shared__ cx<T> hh[MAXM];
-    if (hpart) {
-        // inner product i = sum over the chunk partials: thread (g, i) adds the
-        // chunks c = g mod HG, then thread i adds the HG group sums (fixed order)
-        constexpr int HG = RED_NT / MAXM;
-        __shared__ cx<double> hg[HG][MAXM];
-        const int i = threadIdx.x % MAXM, gq = threadIdx.x / MAXM;
-        if (i < m) {
-            cx<double> hv = czero<double>();
-            for (int q = gq; q < nc; q += HG) hv += hpart[((size_t)r * nc + q) * m + i];
-            hg[gq][i] = hv;
-        }
-        __syncthreads();
-        if (threadIdx.x < m) {
-            cx<double> hv = hg[0][threadIdx.x];
-            for (int q = 1; q < HG; q++) hv += hg[q][threadIdx.x];
-            const double f = scv ? scv[threadIdx.x] : 1.0;
-            hv = f * hv;
-            if (c == 0) hout[(size_t)r * hstride + threadIdx.x] = hv;
-            hh[threadIdx.x] = ccast<T>(f * hv);
-        }
-    } else if (threadIdx.x < m) {
+    if (threadIdx.x < m) {
         const double gi = g ? g[(size_t)r * gstride + threadIdx.x] : 1.0;
         hh[threadIdx.x] = ccast<T>(gi * h[(size_t)r * hstride + threadIdx.x]);
     }
@@ -210,58 +188,68 @@ __global__ void __launch_bounds__(RED_NT) k_update_norm(long n, long chunk, int 
     const long e0 = c * chunk, e1 = (e0 + chunk < n) ? e0 + chunk : n;
     double acc = 0;
     for (long e = e0 + threadIdx.x; e < e1; e += RED_NT) {
-        cx<T> we = wr[e];
-        // basis entries are loaded in batches so that many loads are in flight
-        // (short coarse vectors leave one element per thread: latency bound)
-        for (int i0 = 0; i0 < m; i0 += UN_BATCH) {
-            cx<T> vv[UN_BATCH];
-#pragma unroll
-            for (int u = 0; u < UN_BATCH; u++) vv[u] = (i0 + u < m) ? Vr[(size_t)(i0 + u) * ldv + e] : czero<T>();
-#pragma unroll
-            for (int u = 0; u < UN_BATCH; u++)
-                if (i0 + u < m) we -= hh[i0 + u] * vv[u];
-        }
+        const cx<T> we = project_out(wr[e], Vr + e, ldv, hh, m);
         wr[e] = we;
         if (wcr) wcr[e] = ccast<float>(we);
         acc += (double)norm2(we);
     }
     acc = block_sum256(acc, sh);
     if (threadIdx.x == 0) npart[(size_t)r * nc + c] = cx<double>{acc, 0.0};
-    if (!ga.st) return;
-    // ---- last workgroup of this RHS: norm, Givens update, next basis vector ----
-    __shared__ int last_s;
-    __threadfence();   // this workgroup's w entries, h (chunk 0) and norm partial
-    if (threadIdx.x == 0) last_s = (atomicAdd(ga.done + r, 1) == nc - 1);
-    __syncthreads();
-    if (!last_s) return;
-    __threadfence();
-    double n2 = 0;
-    for (int q = threadIdx.x; q < nc; q += RED_NT) n2 += npart[(size_t)r * nc + q].re;
-    __syncthreads();   // sh is reused
-    n2 = block_sum256(n2, sh);
-    cx<double>* hr = hout + (size_t)r * hstride;
-    if (threadIdx.x == 0) {
-        hr[33] = cx<double>{n2, 0.0};
-        ga.done[r] = 0;
-    }
-    const double f = gm_column_wg(ga.st + r, ga.j, hr, n2, ga.normalize != 0);
-    if (ga.normalize && f != 0.0) {
-        const T ft = T(f);
-        constexpr int B = 8;   // entries per thread in flight
-        for (long q0 = threadIdx.x; q0 < n; q0 += (long)B * RED_NT) {
-            cx<T> v[B];
+}
+
+// The update of a coarsest-level Arnoldi step.  The stored basis vectors carry
+// factors sc_i (V_i = sc_i * stored): the dot partials are of the stored
+// vectors, so h_i = sc_i * sum and w -= sum_i (h_i sc_i) stored_i.
+template <class T>
+__global__ void __launch_bounds__(RED_NT) k_gm_update(long n, long chunk, int nc, int m, const cx<T>* __restrict__ V,
+                                                      long ldv, const cx<double>* __restrict__ hpart, cx<double>* hout,
+                                                      int hstride, cx<T>* __restrict__ w, cx<double>* __restrict__ npart,
+                                                      long ldr, long ldw, Mask mk, const GmDev* st) {
+    const int c = blockIdx.x, r = blockIdx.y;
+    if (!mk.on(r)) return;
+    // inner product i = sum over the chunk partials: thread (g, i) adds the
+    // chunks c = g mod HG (eight loads in flight), then thread i adds the HG
+    // group sums (fixed order)
+    constexpr int HG = RED_NT / MAXM, HB = 8;
+    __shared__ double sh[RED_NT / 64];
+    __shared__ cx<T> hh[MAXM];
+    __shared__ cx<double> hg[HG][MAXM];
+    const int i = threadIdx.x % MAXM, gq = threadIdx.x / MAXM;
+    if (i < m) {
+        cx<double> hv = czero<double>();
+        for (int q0 = gq; q0 < nc; q0 += HB * HG) {
+            cx<double> p[HB];
 #pragma unroll
-            for (int u = 0; u < B; u++) {
-                const long q = q0 + (long)u * RED_NT;
-                v[u] = (q < n) ? wr[q] : czero<T>();
+            for (int u = 0; u < HB; u++) {
+                const int q = q0 + u * HG;
+                p[u] = q < nc ? hpart[((size_t)r * nc + q) * m + i] : czero<double>();
             }
 #pragma unroll
-            for (int u = 0; u < B; u++) {
-                const long q = q0 + (long)u * RED_NT;
-                if (q < n) wr[q] = ft * v[u];
-            }
+            for (int u = 0; u < HB; u++) hv += p[u];
         }
+        hg[gq][i] = hv;
     }
+    __syncthreads();
+    if (threadIdx.x < m) {
+        cx<double> hv = hg[0][threadIdx.x];
+        for (int q = 1; q < HG; q++) hv += hg[q][threadIdx.x];
+        const double f = st[r].sc[threadIdx.x];
+        hv = f * hv;
+        if (c == 0) hout[(size_t)r * hstride + threadIdx.x] = hv;
+        hh[threadIdx.x] = ccast<T>(f * hv);
+    }
+    __syncthreads();
+    const cx<T>* Vr = V + r * ldr;
+    cx<T>* wr = w + r * ldw;
+    const long e0 = c * chunk, e1 = (e0 + chunk < n) ? e0 + chunk : n;
+    double acc = 0;
+    for (long e = e0 + threadIdx.x; e < e1; e += RED_NT) {
+        const cx<T> we = project_out(wr[e], Vr + e, ldv, hh, m);
+        wr[e] = we;
+        acc += (double)norm2(we);
+    }
+    acc = block_sum256(acc, sh);
+    if (threadIdx.x == 0) npart[(size_t)r * nc + c] = cx<double>{acc, 0.0};
 }
 
 static inline cx<double>* hpart_of(void* work) { return (cx<double>*)work; }
@@ -367,9 +355,9 @@ void vec_update_norm(long n, int m, const cx<T>* V, long ldv, const cx<double>* 
         dim3 grid(nc, rb.nr);
         // the FP32 copy is written by the launch that leaves w final
         const bool last = i0 + mm >= m;
-        k_update_norm<T><<<grid, RED_NT, 0, s>>>(n, chunk, nc, mm, V + (size_t)i0 * ldv, ldv, h + i0, rb.ostride, nullptr,
-                                                 nullptr, w, npart_of(work, rb.nr), rb.ldr, rb.ldw, rb.mk, GivensArgs{},
-                                                 g ? g + i0 : nullptr, gstride, last ? wc : nullptr, ldc);
+        k_update_norm<T><<<grid, RED_NT, 0, s>>>(n, chunk, nc, mm, V + (size_t)i0 * ldv, ldv, h + i0, rb.ostride, w,
+                                                 npart_of(work, rb.nr), rb.ldr, rb.ldw, rb.mk, g ? g + i0 : nullptr, gstride,
+                                                 last ? wc : nullptr, ldc);
         i0 += mm;
     } while (i0 < m);
     dim3 g2(1, rb.nr);
@@ -425,62 +413,6 @@ __device__ __forceinline__ cx<double> cdiv(cx<double> a, cx<double> b) {
     return cx<double>{(a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d};
 }
 
-// fold column j (inner products h[0..j], ||w||^2 = hn2) into the state of
-// one RHS, by a whole workgroup (at least 32 threads): the inner
-// products and the previous rotations are first staged in LDS by many
-// threads at once, then one thread runs the rotation chain with the running
-// entry in registers (the global-memory form waits on one load per rotation)
-// Returns, in every thread, the factor that normalises the new basis vector
-// (0 when this RHS stopped at this step: the vector is then left as it is).
-__device__ double gm_column_wg(GmDev* st, int j, const cx<double>* h, double hn2, bool normalize) {
-    __shared__ cx<double> hs[33], css[32], sns[32];
-    __shared__ double sc_s;
-    const int t = threadIdx.x;
-    if (t <= j) hs[t] = h[t];
-    if (t < j) {
-        css[t] = st->cs[t];
-        sns[t] = st->sn[t];
-    }
-    __syncthreads();
-    if (t == 0) {
-        cx<double>* col = st->H + (size_t)j * 33;
-        const double hn = sqrt(hn2);
-        cx<double> a = hs[0];
-        for (int i = 0; i < j; i++) {  // previous rotations; col[i] is final after rotation i
-            const cx<double> b = hs[i + 1];
-            col[i] = conj(css[i]) * a + conj(sns[i]) * b;
-            a = -(sns[i] * a) + css[i] * b;
-        }
-        const cx<double> b = cx<double>{hn, 0.0};
-        const double den = sqrt(norm2(a) + norm2(b));
-        cx<double> c, s;
-        if (den == 0.0) { c = cx<double>{1.0, 0.0}; s = czero<double>(); }
-        else { c = cx<double>{a.re / den, a.im / den}; s = cx<double>{b.re / den, b.im / den}; }
-        st->cs[j] = c;
-        st->sn[j] = s;
-        col[j] = conj(c) * a + conj(s) * b;
-        col[j + 1] = czero<double>();
-        const cx<double> gj = st->g[j];
-        st->g[j + 1] = -(s * gj);
-        st->g[j] = conj(c) * gj;
-        st->its += 1;
-        st->j = j + 1;
-        const double resid = sqrt(norm2(st->g[j + 1]));
-        int stop = 0;
-        if (st->fixed > 0) stop = st->its >= st->fixed;
-        else stop = (resid <= st->tol_abs) || (st->its >= st->maxit);
-        if (hn == 0.0) stop = 1;
-        st->stop = stop;
-        st->scale = (hn > 0) ? 1.0 / hn : 0.0;
-        // the new basis vector: w scaled by the caller (normalize), or w kept
-        // with its factor
-        st->sc[j + 1] = normalize ? 1.0 : st->scale;
-        sc_s = stop ? 0.0 : st->scale;
-    }
-    __syncthreads();
-    return sc_s;
-}
-
 // back substitution R y = g with the rotated Hessenberg R (k x k upper
 // triangle), by columns: once y_i is known every thread r < i removes
 // R_ri y_i from its g_r.  R and g are staged in LDS first (at least 32 threads).
@@ -505,15 +437,16 @@ void gm_start(GmDev* st, const cx<double>* res, int rstride, double tol, int fir
     k_gm_start<<<nr, 64, 0, s>>>(st, res, rstride, tol, first, m, maxit, fixed, mk);
 }
 
-__global__ void k_gm_gather(const GmDev* st, int nr, int* out) {
-    const int r = threadIdx.x;
-    if (r < nr) {
+__global__ void k_gm_gather(GmDev* st, int* out, InScale pend) {
+    const int r = blockIdx.x;
+    if (pend.npart) gm_fold(pend, r);
+    if (threadIdx.x == 0) {   // the thread that wrote the state
         out[3 * r] = st[r].j;
         out[3 * r + 1] = st[r].its;
         out[3 * r + 2] = st[r].stop;
     }
 }
-void gm_gather(const GmDev* st, int nr, int* out, hipStream_t s) { k_gm_gather<<<1, 64, 0, s>>>(st, nr, out); }
+void gm_gather(GmDev* st, int nr, int* out, hipStream_t s, InScale pend) { k_gm_gather<<<nr, 64, 0, s>>>(st, out, pend); }
 void gm_solve(GmDev* st, int nr, hipStream_t s) { k_gm_solve<<<nr, 64, 0, s>>>(st); }
 
 template <class T>
@@ -553,24 +486,35 @@ void vec_lincomb_dev(long n, const cx<T>* V, long ldv, const GmDev* st, cx<T>* x
     k_lincomb_dev<T><<<grid, 256, 0, s>>>(n, V, ldv, st, x, ldr, ldx, assign ? 1 : 0);
 }
 
+// Chunks of the Arnoldi reductions.  Short vectors take one entry per thread:
+// a chunk of 1024 left four dependent rounds of basis loads to each thread and
+// 5 of 256 CUs busy at 16^4.  Every workgroup of the update adds the partials
+// of all chunks, so long vectors keep at most 256.
+static inline int gm_chunks(long n) {
+    const long c = n <= 65536 ? std::min<long>((n + 255) / 256, 64) : std::min<long>((n + 1023) / 1024, 256);
+    return (int)std::max<long>(c, 1);
+}
+
 template <class T>
-void vec_multidot_skip(long n, int m, const cx<T>* V, long ldv, const cx<T>* w, void* work, hipStream_t s,
-                       RedBatch rb) {
-    const int nc = red_chunks(n);
+void gm_dots(long n, int m, const cx<T>* V, long ldv, const cx<T>* w, void* work, hipStream_t s, RedBatch rb) {
+    const int nc = gm_chunks(n);
     const long chunk = (n + nc - 1) / nc;
     dim3 grid(nc, m, rb.nr);
     k_multidot<T><<<grid, RED_NT, 0, s>>>(n, chunk, nc, m, V, ldv, w, hpart_of(work), rb.ldr, rb.ldw, rb.mk);
 }
 
 template <class T>
-void vec_update_norm_givens(long n, int m, const cx<T>* V, long ldv, cx<T>* w, cx<double>* res, void* work,
-                            hipStream_t s, RedBatch rb, GmDev* st, int j, int* done, bool normalize) {
-    const int nc = red_chunks(n);
+void gm_update(long n, int m, const cx<T>* V, long ldv, cx<T>* w, cx<double>* res, void* work, hipStream_t s, RedBatch rb,
+               const GmDev* st) {
+    const int nc = gm_chunks(n);
     const long chunk = (n + nc - 1) / nc;
     dim3 grid(nc, rb.nr);
-    k_update_norm<T><<<grid, RED_NT, 0, s>>>(n, chunk, nc, m, V, ldv, nullptr, rb.ostride, hpart_of(work), res, w,
-                                             npart_of(work, rb.nr), rb.ldr, rb.ldw, rb.mk,
-                                             GivensArgs{st, j, done, normalize ? 1 : 0}, nullptr, 0, nullptr, 0);
+    k_gm_update<T><<<grid, RED_NT, 0, s>>>(n, chunk, nc, m, V, ldv, hpart_of(work), res, rb.ostride, w,
+                                           npart_of(work, rb.nr), rb.ldr, rb.ldw, rb.mk, st);
+}
+
+InScale gm_pending(long n, int j, int which, const GmDev* st, const cx<double>* res, void* work, RedBatch rb) {
+    return InScale{st, j, which, npart_of(work, rb.nr), gm_chunks(n), res, rb.ostride};
 }
 
 template <class T, class X>
@@ -677,9 +621,9 @@ void set_flags(int* d, unsigned bits, int n, hipStream_t s) { k_set_flags<<<1, 6
     template void vec_scale_dev<T>(long, const GmDev*, cx<T>*, hipStream_t, bool, int, long, const cx<T>*);        \
     template void vec_lincomb_dev<T>(long, const cx<T>*, long, const GmDev*, cx<T>*, hipStream_t, int, long, long,  \
                                      bool);                                                                         \
-    template void vec_multidot_skip<T>(long, int, const cx<T>*, long, const cx<T>*, void*, hipStream_t, RedBatch);  \
-    template void vec_update_norm_givens<T>(long, int, const cx<T>*, long, cx<T>*, cx<double>*, void*, hipStream_t, \
-                                            RedBatch, GmDev*, int, int*, bool);
+    template void gm_dots<T>(long, int, const cx<T>*, long, const cx<T>*, void*, hipStream_t, RedBatch);            \
+    template void gm_update<T>(long, int, const cx<T>*, long, cx<T>*, cx<double>*, void*, hipStream_t, RedBatch,       \
+                               const GmDev*);
 
 DD_BLAS_INST(double)
 DD_BLAS_INST(float)

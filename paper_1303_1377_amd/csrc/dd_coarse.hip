@@ -14,7 +14,7 @@
 #include <stdexcept>
 #include <type_traits>
 
-#include "dd_kernels.h"
+#include "dd_gmres.h"
 
 namespace dd {
 
@@ -44,7 +44,11 @@ template <class T, class S>
 __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> op, int par, int self_mode,
                                                                 const cx<T>* __restrict__ in1, int hop_sign,
                                                                 const cx<T>* in2, int post_inv, cx<T>* out,
-                                                                Mask mk, long ld) {
+                                                                Mask mk, long ld, InScale isc, int nsite) {
+    if ((int)blockIdx.x >= nsite) {   // the extra workgroup of a first Arnoldi kernel
+        gm_fold(isc, blockIdx.y);
+        return;
+    }
     if (!mk.on(blockIdx.y)) return;
     {
         const long off = blockIdx.y * ld;
@@ -98,11 +102,16 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
             b[u] = (row && cb + u < c1) ? Ainv[(size_t)(cb + u) * nd] : cx<S>{S(0), S(0)};
     };
     if (post_inv) load_inv(c0);
+    T f1 = T(1), f2 = T(hop_sign < 0 ? -1 : 1);
+    if (isc.st) {
+        const T f = T(gm_factor(isc, blockIdx.y));
+        if (isc.which & 1) f1 *= f;
+        if (isc.which & 2) f2 *= f;
+    }
     __syncthreads();
     for (int e = threadIdx.x; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
-        const cx<T> v = vin[s2][e - s2 * nd];
-        X[e] = (s2 >= nself && hop_sign < 0) ? -v : v;
+        X[e] = ((s2 >= nself) ? f2 : f1) * vin[s2][e - s2 * nd];
     }
     __syncthreads();
     cx<T> acc = czero<T>();
@@ -116,7 +125,7 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
     __syncthreads();
     cx<T> tot = czero<T>();
     if (w == 0 && row) {
-        tot = (self_mode == CS_IDENT) ? in1[gs * nd + r] : czero<T>();
+        tot = (self_mode == CS_IDENT) ? f1 * in1[gs * nd + r] : czero<T>();
         for (int q = 0; q < nw; q++) tot += part[q][r];
     }
     if (!post_inv) {
@@ -306,7 +315,11 @@ template <class S, int NDK = 0>
 __global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op, int par, int self_mode,
                                                            const cx<float>* __restrict__ in1, int hop_sign,
                                                            const cx<float>* in2, int post_inv, cx<float>* out, Mask mk,
-                                                           long ld, int nr) {
+                                                           long ld, int nr, InScale isc, int nsite) {
+    if ((int)blockIdx.x >= nsite) {   // the extra workgroups of a first Arnoldi kernel
+        gm_fold(isc, blockIdx.x - nsite);
+        return;
+    }
     constexpr int K = MfmaK<S>::K;
     extern __shared__ char smem_raw[];
     __shared__ const cx<S>* mat[9];
@@ -335,8 +348,18 @@ __global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op
         mat[nself + t] = op.M + (gs * 9 + 1 + t) * nn;
         vin[nself + t] = in2 + nb_global(g, p, x, t) * nd;
     }
+    // factors of the inputs, per right-hand side (wave w finds every nw-th)
+    __shared__ float fac[2][16];
+    for (int j = t >> 6; j < 16; j += nt >> 6) {
+        const float f = (isc.st && j < nr) ? (float)gm_factor(isc, j) : 1.f;
+        if ((t & 63) == 0) {
+            fac[0][j] = (isc.which & 1) ? f : 1.f;
+            fac[1][j] = (isc.which & 2) ? f : 1.f;
+        }
+    }
     __syncthreads();
     const int ns = nself + (hop_sign != 0 ? 8 : 0);
+    auto staged = [&](int sl, int j, int c) { return fac[sl >= nself][j] * vin[sl][(size_t)j * ld + c]; };
     // stage X_s: entry (s, c, j), c fastest so each RHS column is read contiguously.
     // FP16 form: column j of every X_s is divided by sc[j], the largest modulus
     // of the column's reals over the 9 slots (a first pass over the inputs
@@ -351,7 +374,7 @@ __global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op
             const int sl = e / (xs * ndk), rem = e - sl * xs * ndk;
             const int j = rem / ndk, c = rem - j * ndk;
             if (c < nd && j < nr && mk.on(j)) {
-                const cx<float> v = vin[sl][(size_t)j * ld + c];
+                const cx<float> v = staged(sl, j, c);
                 const float m = fmaxf(fabsf(v.re), fabsf(v.im));
                 if (m > 0.f) atomicMax(reinterpret_cast<int*>(sc) + j, __float_as_int(m));
             }
@@ -361,7 +384,7 @@ __global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op
             const int sl = e / (xs * ndk), rem = e - sl * xs * ndk;
             const int j = rem / ndk, c = rem - j * ndk;
             cx<float> v = czero<float>();
-            if (c < nd && j < nr && mk.on(j)) v = vin[sl][(size_t)j * ld + c];
+            if (c < nd && j < nr && mk.on(j)) v = staged(sl, j, c);
             const float inv = sc[j] > 0.f ? 1.f / sc[j] : 0.f;
             Xre[(sl * ndk + c) * xs + j] = S(v.re * inv);
             Xim[(sl * ndk + c) * xs + j] = S(v.im * inv);
@@ -371,7 +394,7 @@ __global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op
             const int sl = e / (xs * ndk), rem = e - sl * xs * ndk;
             const int j = rem / ndk, c = rem - j * ndk;
             cx<float> v = czero<float>();
-            if (c < nd && j < nr && mk.on(j)) v = vin[sl][(size_t)j * ld + c];
+            if (c < nd && j < nr && mk.on(j)) v = staged(sl, j, c);
             Xre[(sl * ndk + c) * xs + j] = S(v.re);
             Xim[(sl * ndk + c) * xs + j] = S(v.im);
         }
@@ -414,7 +437,7 @@ __global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op
         for (int v = 0; v < 4; v++) {
             const int row = 16 * w + 4 * q + v;
             if (row < nd) {
-                cx<float> a = in1[(size_t)j * ld + gs * nd + row];
+                const cx<float> a = fac[0][j] * in1[(size_t)j * ld + gs * nd + row];
                 cre[v] += a.re;
                 cim[v] += a.im;
             }
@@ -501,7 +524,12 @@ static size_t mfma_lds_bytes(int nd, int nr) {
 template <class T, class S, int RC>
 __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par, int self_mode,
                                                      const cx<T>* __restrict__ in1, int hop_sign, int fold,
-                                                     const cx<T>* in2, cx<T>* out, Mask mk, long ld, InScale isc) {
+                                                     const cx<T>* in2, cx<T>* out, Mask mk, long ld, InScale isc,
+                                                     int nwg) {
+    if ((int)blockIdx.x >= nwg) {   // the extra workgroup of a first Arnoldi kernel
+        gm_fold(isc, blockIdx.y);
+        return;
+    }
     constexpr int CG = 64 / RC;          // column groups per wavefront
     constexpr int PF = (CG >= 4) ? 12 * (8 / CG) : 24;   // block entries a lane loads at once
     if (!mk.on(blockIdx.y)) return;
@@ -552,7 +580,7 @@ __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par,
     // factors of the two inputs (stored GMRES basis vectors carry theirs in the state)
     T f1 = T(1), f2 = T(1);
     if (isc.st) {
-        const T f = T(isc.st[blockIdx.y].sc[isc.j]);
+        const T f = T(gm_factor(isc, blockIdx.y));
         if (isc.which & 1) f1 = f;
         if (isc.which & 2) f2 = f;
     }
@@ -593,8 +621,9 @@ static void launch_rows(const CoarseOp<T, S>& op, int par, int self_mode, const 
     constexpr int RC = 128 / (int)sizeof(cx<S>);   // rows per 128-byte line
     const int nsite = (par < 0) ? 2 * op.g.vh : op.g.vh;
     const int nrc = (op.nd + RC - 1) / RC;
-    dim3 grid(nsite * nrc, nr);
-    k_coarse_rows<T, S, RC><<<grid, 256, 0, s>>>(op, par, self_mode, in1, hop_sign, fold, in2, out, mk, ld, isc);
+    dim3 grid(nsite * nrc + (isc.npart ? 1 : 0), nr);
+    k_coarse_rows<T, S, RC><<<grid, 256, 0, s>>>(op, par, self_mode, in1, hop_sign, fold, in2, out, mk, ld, isc,
+                                                 nsite * nrc);
 }
 
 // B_k(x) = Minv(x) M_{1+k}(x): workgroup (even site i, hop k), FP64 sums
@@ -636,20 +665,19 @@ template <class T, class S>
 void coarse_apply(const CoarseOp<T, S>& op, int par, int self_mode, const cx<T>* in1, int hop_sign, const cx<T>* in2,
                   bool post_inv, cx<T>* out, hipStream_t s, Mask mk, int nr, long ld, InScale isc) {
     const bool rows = !post_inv && self_mode != CS_SELFINV && op.nd <= 64;
-    if (isc.st && (coarse_uses_mfma(op, nr) || !rows))
-        throw std::invalid_argument("coarse_apply: scaled inputs need the row-split vector-unit form");
     int nsite = (par < 0) ? 2 * op.g.vh : op.g.vh;
     if constexpr (std::is_same<T, float>::value) {
         // the matrix-core form serves FP32 arithmetic with 2..16 right-hand sides and nd <= 64
         if (op.mfma && nr >= 2 && nr <= 16 && op.nd <= 64) {
             constexpr int K = MfmaK<S>::K;
             constexpr int NDK40 = (40 + K - 1) / K * K;
+            const int extra = isc.npart ? nr : 0;
             if (op.nd == 40)
-                k_coarse_apply_mfma<S, NDK40><<<nsite, 64 * 3, mfma_lds_bytes<S>(op.nd, nr), s>>>(
-                    op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr);
+                k_coarse_apply_mfma<S, NDK40><<<nsite + extra, 64 * 3, mfma_lds_bytes<S>(op.nd, nr), s>>>(
+                    op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr, isc, nsite);
             else
-                k_coarse_apply_mfma<S><<<nsite, 64 * ((op.nd + 15) / 16), mfma_lds_bytes<S>(op.nd, nr), s>>>(
-                    op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr);
+                k_coarse_apply_mfma<S><<<nsite + extra, 64 * ((op.nd + 15) / 16), mfma_lds_bytes<S>(op.nd, nr), s>>>(
+                    op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr, isc, nsite);
             return;
         }
     }
@@ -667,8 +695,9 @@ void coarse_apply(const CoarseOp<T, S>& op, int par, int self_mode, const cx<T>*
     // workgroup size allows
     int nw = std::max(1, std::min(CA_WAVES, (nslot * op.nd + CaPre<S>::N - 1) / CaPre<S>::N));
     if (post_inv) nw = std::max(nw, std::min(CA_WAVES, (op.nd + CaPre<S>::INV - 1) / CaPre<S>::INV));
-    dim3 grid(nsite, nr);
-    k_coarse_apply<T, S><<<grid, 64 * nw, 0, s>>>(op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld);
+    dim3 grid(nsite + (isc.npart ? 1 : 0), nr);
+    k_coarse_apply<T, S><<<grid, 64 * nw, 0, s>>>(op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, isc,
+                                                  nsite);
 }
 
 // ---------------------------------------------------------------------------

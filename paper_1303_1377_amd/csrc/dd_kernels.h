@@ -164,12 +164,19 @@ enum CoarseSelf { CS_NONE = 0, CS_IDENT = 1, CS_SELF = 2, CS_SELFINV = 3 };
 // for the sites of parity `par` (0, 1) or all sites (par < 0).
 // input scaling of the coarse stencil: the inputs flagged in `which` (1: in1,
 // 2: in2) of right-hand side r are multiplied by st[r].sc[j] (GMRES basis
-// vectors stored without their normalisation); vector-unit forms only
+// vectors stored without their normalisation).  With npart, vector j is the
+// one the step before made: its factor comes from the nc partial norms, and
+// one extra workgroup per right-hand side folds column j - 1 (inner products
+// at h + r hstride) into the state (see dd_gmres.h).
 struct GmDev;
 struct InScale {
     const GmDev* st = nullptr;
     int j = 0;
     int which = 0;
+    const cx<double>* npart = nullptr;
+    int nc = 0;
+    const cx<double>* h = nullptr;
+    int hstride = 0;
 };
 template <class T, class S>
 void coarse_apply(const CoarseOp<T, S>& op, int par, int self_mode, const cx<T>* in1, int hop_sign, const cx<T>* in2,
@@ -297,8 +304,9 @@ struct alignas(16) GmDev {
 // on a restart (first = 0) a stopped one keeps its iteration count and gets j = 0.
 void gm_start(GmDev* st, const cx<double>* res, int rstride, double tol, int first, int m, int maxit, int fixed,
               int nr, hipStream_t s, Mask mk = all_rhs());
-// out[3r..3r+2] = {j, its, stop} of st[r] (one small transfer reads a batch)
-void gm_gather(const GmDev* st, int nr, int* out, hipStream_t s);
+// out[3r..3r+2] = {j, its, stop} of st[r] (one small transfer reads a batch);
+// with pend.npart the column pend.j - 1 that the last step left is folded first
+void gm_gather(GmDev* st, int nr, int* out, hipStream_t s, InScale pend = InScale{});
 // y = R^{-1} g for the st->j columns of the cycle
 void gm_solve(GmDev* st, int nr, hipStream_t s);
 // x_r = st[r].scale * (src_r, or x_r itself when src is null) (skipped once
@@ -310,18 +318,17 @@ void vec_scale_dev(long n, const GmDev* st, cx<T>* x, hipStream_t s, bool ignore
 template <class T>
 void vec_lincomb_dev(long n, const cx<T>* V, long ldv, const GmDev* st, cx<T>* x, hipStream_t s, int nr = 1,
                      long ldr = 0, long ldx = 0, bool assign = false);
-// Arnoldi reductions of the device-resident GMRES (RHS with st[r].stop skip)
+// The two reductions of an Arnoldi step of the device-resident GMRES (RHS with
+// st[r].stop skip): chunk partials of (stored V_i)^H w for i < m, then
+// w -= sum_i h_i V_i with h_i = sc_i (stored V_i)^H w summed from them (written
+// to res + r*ostride) and the chunk partials of ||w||^2, which the next step
+// reads (gm_pending describes them).  w becomes the next basis vector as it
+// is; its factor 1/||w|| is kept in the state.
 template <class T>
-void vec_multidot_skip(long n, int m, const cx<T>* V, long ldv, const cx<T>* w, void* work, hipStream_t s,
-                       RedBatch rb);
-// w -= sum_i h_i V_i with h_i = sc_i (stored V_i)^H w summed from the multidot
-// partials (written to res + r*ostride), ||w||^2, and then, in the last
-// workgroup of each RHS to finish (counter done[r], left at 0), the Givens
-// update of column j; w becomes the next basis vector: scaled by the last
-// workgroup when `normalize`, else stored as is with sc[j+1] = 1/||w||.
-// Stopped RHS are skipped.
+void gm_dots(long n, int m, const cx<T>* V, long ldv, const cx<T>* w, void* work, hipStream_t s, RedBatch rb);
 template <class T>
-void vec_update_norm_givens(long n, int m, const cx<T>* V, long ldv, cx<T>* w, cx<double>* res, void* work,
-                            hipStream_t s, RedBatch rb, GmDev* st, int j, int* done, bool normalize);
+void gm_update(long n, int m, const cx<T>* V, long ldv, cx<T>* w, cx<double>* res, void* work, hipStream_t s, RedBatch rb,
+               const GmDev* st);
+InScale gm_pending(long n, int j, int which, const GmDev* st, const cx<double>* res, void* work, RedBatch rb);
 
 }  // namespace dd

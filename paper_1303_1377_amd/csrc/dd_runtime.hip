@@ -193,9 +193,7 @@ static const int DI_ONES = 16;      // MAX_RHS words that stay 1: "every RHS act
 static const int DI_GATHER = 32;    // {j, its, stop} of each coarsest-GMRES state
 static const int DI_BAR = 120;      // cooperative GMRES: barrier count, generation, abort flag
 static const int DI_MASK = 128;     // per level: [cycle mask][current mask], MAX_RHS each
-static const int DI_DONE = DI_MASK + 2 * MAX_RHS * DD_MAXLEV;   // coarsest GMRES: finished-workgroup
-                                                                 // counts, one per RHS (kept at 0)
-static const int DI_WORDS = DI_DONE + MAX_RHS;
+static const int DI_WORDS = DI_MASK + 2 * MAX_RHS * DD_MAXLEV;
 // reduction results per right-hand side: pass-1 h (0..32), ||w||^2 (33),
 // pass-2 h (34..66), ||w||^2 (67)
 static const int RS = 136;
@@ -896,40 +894,45 @@ void Hier<T>::gmres_oe(int l, const cx<T>* r, cx<T>* e, const Batch& bt) {
     vec_scale_dev<T>(nred, st, odd(V), C->s, true, nr, nfull, odd(f));
     bool first_cycle = true;
     int* hs = C->hint + DI_GATHER;
-    auto read_state = [&]() {
-        gm_gather(st, nr, C->dflags + DI_GATHER, C->s);
+    const RedBatch rb{nr, nfull, nfull, RS, live};
+    // columns done (jd): the last one is still to be folded into the states
+    auto read_state = [&](int jd) {
+        gm_gather(st, nr, C->dflags + DI_GATHER, C->s,
+                  jd > 0 ? gm_pending(nred, jd, 0, st, C->dred, C->dwork, rb) : InScale{});
         HIPX(hipMemcpyAsync(hs, C->dflags + DI_GATHER, 3 * sizeof(int) * nr, hipMemcpyDeviceToHost, C->s));
         sync(C);
         for (int q = 0; q < nr; q++)
             if (!hs[3 * q + 2]) return false;
         return true;
     };
-    const RedBatch rb{nr, nfull, nfull, RS, live};
     // one Arnoldi step of every running RHS, enqueued on stream `sq`
-    // (the Prof brackets record nothing while a graph is being captured)
-    auto arnoldi_step = [&](int j, hipStream_t sq) {
+    // (the Prof brackets record nothing while a graph is being captured).
+    // Basis vectors stay unnormalised, their factors scale the stencil's inputs
+    // (no pass over w to normalise it); `pend`: the step before was enqueued
+    // with this one, so its column is folded here
+    auto arnoldi_step = [&](int j, bool pend, hipStream_t sq) {
         cx<T>* vj = V + (size_t)j * ldv;
         cx<T>* w = V + (size_t)(j + 1) * ldv;
+        auto first = [&](int which) {
+            return pend ? gm_pending(nred, j, which, st, C->dred, C->dwork, rb) : InScale{st, j, which};
+        };
         {
             Prof pr(C, DD_K_COARSE, 2 * by_coarse(l, 9, 2, false, k));
             with_coarse(l, [&](auto& op) {
-                // vector-unit forms: basis vectors stay unnormalised, their factors
-                // scale the stencil's inputs (no pass over w to normalise it)
                 if (full) {
-                    coarse_apply(op, -1, CS_SELF, vj, 1, vj, false, w, sq, live, nr, nfull);
+                    coarse_apply(op, -1, CS_SELF, vj, 1, vj, false, w, sq, live, nr, nfull, first(3));
                 } else if (folded) {
-                    coarse_apply_folded(op, (const cx<T>*)nullptr, 1, vj, wc[l], sq, live, nr, nfull, InScale{st, j, 2});
+                    coarse_apply_folded(op, (const cx<T>*)nullptr, 1, vj, wc[l], sq, live, nr, nfull, first(2));
                     coarse_apply(op, 1, CS_SELF, vj, -1, wc[l], false, w, sq, live, nr, nfull, InScale{st, j, 1});
                 } else {
-                    coarse_apply(op, 0, CS_NONE, (const cx<T>*)nullptr, 1, vj, true, wc[l], sq, live, nr, nfull);
-                    coarse_apply(op, 1, CS_SELF, vj, -1, wc[l], false, w, sq, live, nr, nfull);
+                    coarse_apply(op, 0, CS_NONE, (const cx<T>*)nullptr, 1, vj, true, wc[l], sq, live, nr, nfull, first(2));
+                    coarse_apply(op, 1, CS_SELF, vj, -1, wc[l], false, w, sq, live, nr, nfull, InScale{st, j, 1});
                 }
             });
         }
         Prof pr(C, DD_K_REDUCE, 2 * by_reduce(nred, j + 1, k));
-        vec_multidot_skip<T>(nred, j + 1, odd(V), ldv, odd(w), C->dwork, sq, rb);
-        vec_update_norm_givens<T>(nred, j + 1, odd(V), ldv, odd(w), C->dred, C->dwork, sq, rb, st, j, C->dflags + DI_DONE,
-                                  !folded);
+        gm_dots<T>(nred, j + 1, odd(V), ldv, odd(w), C->dwork, sq, rb);
+        gm_update<T>(nred, j + 1, odd(V), ldv, odd(w), C->dred, C->dwork, sq, rb, st);
     };
     // graphs need a capture stream; live kernel timing brackets single launches
     const bool use_graphs = (C->sched & SCHED_GRAPH) && C->cap;
@@ -962,7 +965,7 @@ void Hier<T>::gmres_oe(int l, const cx<T>* r, cx<T>* e, const Batch& bt) {
                 });
             }
             if (herr == hipSuccess) {
-                all_stop = read_state();
+                all_stop = read_state(0);
                 if (read_flag(C, DI_BAR + 2)) {
                     // a barrier wait gave up (workgroups not co-resident): redo this
                     // coarse solve with single launches and keep them from now on
@@ -989,7 +992,7 @@ void Hier<T>::gmres_oe(int l, const cx<T>* r, cx<T>* e, const Batch& bt) {
                     hipGraphExec_t ex = nullptr;
                     HIPX(hipStreamBeginCapture(C->cap, hipStreamCaptureModeThreadLocal));
                     C->capturing = true;
-                    for (int q = j; q < jend; q++) arnoldi_step(q, C->cap);
+                    for (int q = j; q < jend; q++) arnoldi_step(q, q > j, C->cap);
                     C->capturing = false;
                     HIPX(hipStreamEndCapture(C->cap, &gr));
                     hipError_t e = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
@@ -1003,9 +1006,9 @@ void Hier<T>::gmres_oe(int l, const cx<T>* r, cx<T>* e, const Batch& bt) {
                 HIPX(hipGraphLaunch(it->second, C->s));
                 j = jend;
             } else {
-                for (; j < jend; j++) arnoldi_step(j, C->s);
+                for (const int j0 = j; j < jend; j++) arnoldi_step(j, j > j0, C->s);
             }
-            if (read_state()) { all_stop = true; break; }
+            if (read_state(jend)) { all_stop = true; break; }
             chunk = 4;
         }
         gm_solve(st, nr, C->s);
@@ -1023,7 +1026,7 @@ void Hier<T>::gmres_oe(int l, const cx<T>* r, cx<T>* e, const Batch& bt) {
         vec_multidot<T>(nred, 1, odd(V), 0, odd(V), C->dred, C->dwork, nullptr, C->s, rb);
         gm_start(st, C->dred, RS, p.coarse_tol, 0, m, p.coarse_maxit, p.coarse_fixed, nr, C->s);
         vec_scale_dev<T>(nred, st, odd(V), C->s, false, nr, nfull);
-        if (read_state()) break;
+        if (read_state(0)) break;
         chunk = 4;
     }
     // e_e = A_ee^{-1} (r_e - D_eo e_o)  (= t_e - B e_o with the folded blocks)
