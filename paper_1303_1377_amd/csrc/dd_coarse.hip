@@ -156,7 +156,8 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
 //     C (nd x k) += M_s (nd x nd) X_s (nd x k),   s = self + 8 hops,
 // which runs as real MFMA tiles on the split real / imaginary parts:
 //     C_re += M_re X_re - M_im X_im,   C_im += M_re X_im + M_im X_re.
-// Workgroup = one site; wave w owns rows [16w, 16w+16) of C (nd <= 64).  The
+// Up to eight right-hand sides take one tile for both parts (half the
+// instructions).  Workgroup = one site; a wave owns 16 rows of C (nd <= 64).  The
 // k right-hand-side columns of every X_s are staged once in LDS (one coalesced
 // pass per RHS), so each block entry is read once for all right-hand sides.
 // The FP32 form uses v_mfma_f32_16x16x4_f32 on FP32 blocks; the FP16-storage
@@ -184,332 +185,389 @@ __device__ __forceinline__ f32x4 mma(f16x4 a, f16x4 b, f32x4 c) {
 // workgroups share a CU
 __host__ __device__ __forceinline__ int mfma_cols(int nr) { return nr <= 4 ? 4 : (nr <= 8 ? 8 : 16); }
 
-// A fragment of a column-major nd x nd block: row r, columns c0 .. c0+K/4-1
-// of this lane's k-slice; zero outside the block.
-template <class S>
-__device__ __forceinline__ void a_frag(const cx<S>* __restrict__ A, int nd, int r, int c0, float sgn,
-                                       typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type& re,
-                                       typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type& im) {
-    if constexpr (std::is_same<S, float>::value) {
-        cx<float> a = (r < nd && c0 < nd) ? A[(size_t)c0 * nd + r] : czero<float>();
-        re = sgn * a.re;
-        im = sgn * a.im;
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int c = c0 + q;
-            cx<_Float16> a = (r < nd && c < nd) ? A[(size_t)c * nd + r] : cx<_Float16>{_Float16(0), _Float16(0)};
-            re[q] = sgn > 0 ? a.re : _Float16(-a.re);
-            im[q] = sgn > 0 ? a.im : _Float16(-a.im);
-        }
-    }
-}
-
-// B fragment from the staged X [ndk][xs] (split re / im planes of type S):
-// xs columns are staged (the batch rounded up to 4, 8 or 16); the lanes of
-// the tile's other columns take zeros
-template <class S>
-__device__ __forceinline__ void b_frag(const S* __restrict__ Xre, const S* __restrict__ Xim, int c0, int j, int xs,
-                                       typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type& re,
-                                       typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type& im) {
-    const bool on = j < xs;
-    if constexpr (std::is_same<S, float>::value) {
-        re = on ? Xre[c0 * xs + j] : 0.f;
-        im = on ? Xim[c0 * xs + j] : 0.f;
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            re[q] = on ? Xre[(c0 + q) * xs + j] : _Float16(0);
-            im[q] = on ? Xim[(c0 + q) * xs + j] : _Float16(0);
-        }
-    }
-}
-
-// C += A X over the ndk rows of X for one 16-row tile
-template <class S>
-__device__ __forceinline__ void tile_mma(const cx<S>* __restrict__ A, int nd, int ndk, int r, int lane, float sgn,
-                                         const S* Xre, const S* Xim, int xs, f32x4& cre, f32x4& cim) {
-    constexpr int K = MfmaK<S>::K;
-    constexpr int KL = K / 4;   // k entries per lane
-    const int q = lane >> 4, j = lane & 15;
-    for (int k0 = 0; k0 < ndk; k0 += K) {
-        const int c0 = k0 + q * KL;
-        typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type are, aim, bre, bim, naim;
-        a_frag<S>(A, nd, r, c0, sgn, are, aim);
-        b_frag<S>(Xre, Xim, c0, j, xs, bre, bim);
-        naim = -aim;
-        cre = mma(are, bre, cre);
-        cre = mma(naim, bim, cre);
-        cim = mma(are, bim, cim);
-        cim = mma(aim, bre, cim);
-    }
-}
-
-// The same for a compile-time padded extent NDK (the production nd = 40): all
-// A fragments of the block are loaded before the first product, so a wave has
-// NDK / K loads in flight instead of one per instruction step.
-template <class S, int NDK>
-__device__ __forceinline__ void tile_mma_fixed(const cx<S>* __restrict__ A, int nd, int r, int lane, float sgn,
-                                               const S* Xre, const S* Xim, int xs, f32x4& cre, f32x4& cim) {
-    constexpr int K = MfmaK<S>::K;
-    constexpr int KL = K / 4;
-    constexpr int NS = NDK / K;
-    const int q = lane >> 4, j = lane & 15;
-    typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type are[NS], aim[NS];
-#pragma unroll
-    for (int t = 0; t < NS; t++) a_frag<S>(A, nd, r, t * K + q * KL, sgn, are[t], aim[t]);
-#pragma unroll
-    for (int t = 0; t < NS; t++) {
-        typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type bre, bim, naim;
-        b_frag<S>(Xre, Xim, t * K + q * KL, j, xs, bre, bim);
-        naim = -aim[t];
-        cre = mma(are[t], bre, cre);
-        cre = mma(naim, bim, cre);
-        cim = mma(are[t], bim, cim);
-        cim = mma(aim[t], bre, cim);
-    }
-}
-
-// Fragments of one block for tile_mma_fixed, loaded ahead of their products
-// so that the next block's loads overlap the current block's MFMA work.
-template <class S, int NDK>
+// The A fragments of one block for the wave's tile: rows r = 16 w + (lane & 15),
+// k-slices of NS instruction steps.  Outside the block the last row or column is
+// read again (no branch around a load): rows past it are never stored, columns
+// past it meet rows of X that hold zeros.
+template <class S, int NS>
 struct TileFrags {
-    static constexpr int NS = NDK / MfmaK<S>::K;
-    typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type re[NS], im[NS];
-};
-template <class S, int NDK>
-__device__ __forceinline__ void tile_load(const cx<S>* __restrict__ A, int nd, int r, int lane, float sgn,
-                                          TileFrags<S, NDK>& f) {
-    constexpr int K = MfmaK<S>::K, KL = K / 4;
-    const int q = lane >> 4;
+    using F = typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type;
+    F re[NS], im[NS];
+    __device__ __forceinline__ void load(const cx<S>* __restrict__ A, int nd, int r, int q, int t0 = 0, int step = 1) {
+        constexpr int KL = MfmaK<S>::K / 4;
 #pragma unroll
-    for (int t = 0; t < TileFrags<S, NDK>::NS; t++) a_frag<S>(A, nd, r, t * K + q * KL, sgn, f.re[t], f.im[t]);
-}
-template <class S, int NDK>
-__device__ __forceinline__ void tile_product(const TileFrags<S, NDK>& f, int lane, const S* Xre, const S* Xim, int xs,
-                                             f32x4& cre, f32x4& cim) {
-    constexpr int K = MfmaK<S>::K, KL = K / 4;
-    const int q = lane >> 4, j = lane & 15;
+        for (int t = 0; t < NS; t++) {
+            const int c0 = (t0 + t * step) * MfmaK<S>::K + q * KL;
+            if constexpr (std::is_same<S, float>::value) {
+                const cx<float> a = A[min(c0, nd - 1) * nd + min(r, nd - 1)];
+                re[t] = a.re;
+                im[t] = a.im;
+            } else {
 #pragma unroll
-    for (int t = 0; t < TileFrags<S, NDK>::NS; t++) {
-        typename std::conditional<std::is_same<S, float>::value, float, f16x4>::type bre, bim, naim;
-        b_frag<S>(Xre, Xim, t * K + q * KL, j, xs, bre, bim);
-        naim = -f.im[t];
-        cre = mma(f.re[t], bre, cre);
-        cre = mma(naim, bim, cre);
-        cim = mma(f.re[t], bim, cim);
-        cim = mma(f.im[t], bre, cim);
+                for (int u = 0; u < 4; u++) {
+                    const cx<_Float16> a = A[min(c0 + u, nd - 1) * nd + min(r, nd - 1)];
+                    re[t][u] = a.re;
+                    im[t][u] = a.im;
+                }
+            }
+        }
     }
-}
+    // C += A X for X staged as [row][2 xs] reals: columns j < xs the real, xs + j the
+    // imaginary parts of right-hand side j.  PACK (xs <= 8): one tile holds both,
+    //   [C_re | C_im] += A_re [X_re | X_im] + A_im [-X_im | X_re],
+    // two instructions per step; otherwise two tiles and four instructions.
+    template <bool PACK>
+    __device__ __forceinline__ void multiply(const S* __restrict__ X, int xs, int lane, f32x4& c0, f32x4& c1, int t0 = 0,
+                                             int step = 1) const {
+        constexpr int K = MfmaK<S>::K, KL = K / 4;
+        const int q = lane >> 4, j = lane & 15, cols = 2 * xs;
+        auto frag = [&](int t, int col, bool on) {
+            const S* x = X + ((t0 + t * step) * K + q * KL) * cols + col;
+            if constexpr (std::is_same<S, float>::value) {
+                return on ? x[0] : 0.f;
+            } else {
+                f16x4 v = {};
+                if (on)
+#pragma unroll
+                    for (int u = 0; u < 4; u++) v[u] = x[u * cols];
+                return v;
+            }
+        };
+        if constexpr (PACK) {
+            const bool on = j < cols;
+            const bool lo = j < xs;
+            const int js = lo ? j + xs : j - xs;
+#pragma unroll
+            for (int t = 0; t < NS; t++) {
+                const F b = frag(t, j, on);
+                F s = frag(t, js, on);
+                s = lo ? -s : s;
+                c0 = mma(re[t], b, c0);
+                c0 = mma(im[t], s, c0);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < NS; t++) {
+                const F br = frag(t, j, true), bi = frag(t, xs + j, true), ni = -im[t];
+                c0 = mma(re[t], br, c0);
+                c0 = mma(ni, bi, c0);
+                c1 = mma(re[t], bi, c1);
+                c1 = mma(im[t], br, c1);
+            }
+        }
+    }
+};
 
-// the k x ndk tile product of one block: the unrolled form where the padded
-// extent is the production one (NDK > 0), the loop otherwise
-template <class S, int NDK>
-__device__ __forceinline__ void tile_any(const cx<S>* __restrict__ A, int nd, int ndk, int r, int lane, float sgn,
-                                         const S* Xre, const S* Xim, int xs, f32x4& cre, f32x4& cim) {
-    if constexpr (NDK > 0) tile_mma_fixed<S, NDK>(A, nd, r, lane, sgn, Xre, Xim, xs, cre, cim);
-    else tile_mma<S>(A, nd, ndk, r, lane, sgn, Xre, Xim, xs, cre, cim);
-}
-
-template <class S, int NDK = 0>
-__global__ void __launch_bounds__(256) k_coarse_apply_mfma(CoarseOp<float, S> op, int par, int self_mode,
-                                                           const cx<float>* __restrict__ in1, int hop_sign,
-                                                           const cx<float>* in2, int post_inv, cx<float>* out, Mask mk,
-                                                           long ld, int nr, InScale isc, int nsite) {
+// Waves: (row tile, slot group): group g of MG multiplies the slots g, g + MG,
+// ...; the groups' partial tiles meet in LDS.
+//   MG = 3: a wave loads the fragments of all its slots before anything else, so
+//   the whole panel of the site is in flight while its inputs are staged.  For
+//   lattices of few sites, where one site's latency is the launch's: 64x32^3
+//   coarsest level (256 sites a launch, FP32, four RHS) 20 -> 14 us.
+//   MG = 1: small workgroups that load one block ahead; eight share a CU and hide
+//   each other's waits, which beats the deeper loads once every CU has several
+//   sites: 64x32^3 level 1 (8192 sites) 284 -> 213 us (4.4 TB/s), against 360 us
+//   for MG = 3.
+// The line between them is 1024 sites, four for each CU.
+template <class S, int NS, int MG> struct MfmaWg {
+    static constexpr int NT = 64 * MG * ((NS * MfmaK<S>::K + 15) / 16);
+};
+// ND: the unknowns per site where they are known to the compiler (0: op.nd)
+template <class S, int NS, bool PACK, int ND, int MG>
+__global__ void __launch_bounds__((MfmaWg<S, NS, MG>::NT)) k_coarse_apply_mfma(CoarseOp<float, S> op, int par, int self_mode,
+                                                                   const cx<float>* __restrict__ in1, int hop_sign,
+                                                                   const cx<float>* in2, int post_inv, cx<float>* out,
+                                                                   Mask mk, long ld, int nr, InScale isc, int nsite) {
     if ((int)blockIdx.x >= nsite) {   // the extra workgroups of a first Arnoldi kernel
         gm_fold(isc, blockIdx.x - nsite);
         return;
     }
-    constexpr int K = MfmaK<S>::K;
-    extern __shared__ char smem_raw[];
-    __shared__ const cx<S>* mat[9];
-    __shared__ const cx<float>* vin[9];
+    constexpr int K = MfmaK<S>::K, NDK = NS * K;
+    constexpr bool F16 = std::is_same<S, _Float16>::value;
+    constexpr int NSI = (NS + MG - 1) / MG;         // steps of the inverse block per group
+    extern __shared__ __align__(16) char smem_raw[];
+    __shared__ float fac[2][16], sc[16];
     const Geom g = op.g;
-    const int nd = op.nd;
-    const int ndk = (nd + K - 1) / K * K;          // k extent padded to the instruction
-    const int xs = mfma_cols(nr);                   // staged columns
-    S* Xre = reinterpret_cast<S*>(smem_raw);        // [9][ndk][xs]
-    S* Xim = Xre + 9 * ndk * xs;
+    const int nd = ND ? ND : op.nd, xs = mfma_cols(nr), cols = 2 * xs;
+    const int ntile = (nd + 15) / 16;
+    S* X = reinterpret_cast<S*>(smem_raw);          // [9][NDK][cols]
+    f32x4* red = reinterpret_cast<f32x4*>(X + 9 * NDK * cols);   // [MG - 1][ntile][PACK ? 1 : 2][64]
     int p, i;
     if (par < 0) { p = blockIdx.x >= g.vh; i = blockIdx.x - p * g.vh; }
     else { p = par; i = blockIdx.x; }
     const size_t gs = (size_t)p * g.vh + i;
     const size_t nn = (size_t)nd * nd;
-    const int t = threadIdx.x, nt = blockDim.x;
-    // block and input of every slot: thread k < 8 finds neighbour k
+    const int t = threadIdx.x, nt = blockDim.x, nw = nt >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, q = lane >> 4, j = lane & 15;
+    const int w = wv % ntile, grp = wv / ntile;
+    const int r = 16 * w + j;
     const int nself = (self_mode == CS_SELF || self_mode == CS_SELFINV) ? 1 : 0;
-    if (t == 0 && nself) {
-        mat[0] = (self_mode == CS_SELF) ? op.M + gs * 9 * nn : op.Minv + gs * nn;
-        vin[0] = in1 + gs * nd;
-    }
-    if (hop_sign != 0 && t < 8) {
-        int x[4];
-        cb_coords(g, p, i, x);
-        mat[nself + t] = op.M + (gs * 9 + 1 + t) * nn;
-        vin[nself + t] = in2 + nb_global(g, p, x, t) * nd;
-    }
-    // factors of the inputs, per right-hand side (wave w finds every nw-th)
-    __shared__ float fac[2][16];
-    for (int j = t >> 6; j < 16; j += nt >> 6) {
-        const float f = (isc.st && j < nr) ? (float)gm_factor(isc, j) : 1.f;
-        if ((t & 63) == 0) {
-            fac[0][j] = (isc.which & 1) ? f : 1.f;
-            fac[1][j] = (isc.which & 2) ? f : 1.f;
-        }
-    }
-    __syncthreads();
     const int ns = nself + (hop_sign != 0 ? 8 : 0);
-    auto staged = [&](int sl, int j, int c) { return fac[sl >= nself][j] * vin[sl][(size_t)j * ld + c]; };
-    // stage X_s: entry (s, c, j), c fastest so each RHS column is read contiguously.
-    // FP16 form: column j of every X_s is divided by sc[j], the largest modulus
-    // of the column's reals over the 9 slots (a first pass over the inputs
-    // finds it), so that the rounded inputs lie in [-1, 1] whatever the
-    // vector's magnitude; the products are scaled back in FP32.
-    constexpr bool F16 = std::is_same<S, _Float16>::value;
-    __shared__ float sc[16];
-    if constexpr (F16) {
-        if (t < 16) sc[t] = 0.f;
-        __syncthreads();
-        for (int e = t; e < ns * xs * ndk; e += nt) {
-            const int sl = e / (xs * ndk), rem = e - sl * xs * ndk;
-            const int j = rem / ndk, c = rem - j * ndk;
-            if (c < nd && j < nr && mk.on(j)) {
-                const cx<float> v = staged(sl, j, c);
-                const float m = fmaxf(fabsf(v.re), fabsf(v.im));
-                if (m > 0.f) atomicMax(reinterpret_cast<int*>(sc) + j, __float_as_int(m));
-            }
+    // lane k holds flag and factor of right-hand side k: one load for all
+    const bool mine = lane < nr && mk.on(lane);
+    double f0 = (isc.st && !isc.npart && lane < nr) ? isc.st[lane].sc[isc.j] : 1.0;
+    const unsigned on = (unsigned)__ballot(mine);
+    // Staging of X: wave wv takes the slots wv, wv + nw, ... (its neighbour is
+    // uniform), entries lane, lane + 64, ... of [RHS][row], row fastest so each
+    // input is read contiguously.  Loads return in order, so the inputs of the
+    // first PS slots (SR entries a lane) are asked for before the block fragments.
+    constexpr int SR = 3, PS = MG == 1 ? 3 : 1;   // entries per slot and slots asked for ahead
+    int x[4];
+    cb_coords(g, p, i, x);
+    auto input = [&](int sl) {
+        return sl < nself ? in1 + gs * nd : in2 + nb_global(g, p, x, sl - nself) * nd;
+    };
+    auto entry = [&](const cx<float>* v, int e) {
+        const int k = e / NDK, c = e - k * NDK;
+        return (k < nr && c < nd && ((on >> k) & 1u)) ? v[(size_t)k * ld + c] : czero<float>();
+    };
+    cx<float> pre[PS][SR];
+#pragma unroll
+    for (int a = 0; a < PS; a++)
+        if (wv + a * nw < ns) {
+            const cx<float>* v = input(wv + a * nw);
+#pragma unroll
+            for (int u = 0; u < SR; u++) pre[a][u] = entry(v, lane + 64 * u);
         }
-        __syncthreads();
-        for (int e = t; e < ns * xs * ndk; e += nt) {
-            const int sl = e / (xs * ndk), rem = e - sl * xs * ndk;
-            const int j = rem / ndk, c = rem - j * ndk;
-            cx<float> v = czero<float>();
-            if (c < nd && j < nr && mk.on(j)) v = staged(sl, j, c);
-            const float inv = sc[j] > 0.f ? 1.f / sc[j] : 0.f;
-            Xre[(sl * ndk + c) * xs + j] = S(v.re * inv);
-            Xim[(sl * ndk + c) * xs + j] = S(v.im * inv);
+    // factors of the inputs; the hop sign goes into them
+    auto put_factor = [&](int k, double fk) {
+        const float s = (float)fk;
+        fac[0][k] = (isc.which & 1) ? s : 1.f;
+        fac[1][k] = ((isc.which & 2) ? s : 1.f) * (hop_sign < 0 ? -1.f : 1.f);
+        sc[k] = 0.f;
+    };
+    if (isc.npart) {
+        for (int k = wv; k < nr; k += nw) {
+            const double fk = gm_factor(isc, k);
+            if (lane == 0) put_factor(k, fk);
         }
-    } else {
-        for (int e = t; e < ns * xs * ndk; e += nt) {
-            const int sl = e / (xs * ndk), rem = e - sl * xs * ndk;
-            const int j = rem / ndk, c = rem - j * ndk;
-            cx<float> v = czero<float>();
-            if (c < nd && j < nr && mk.on(j)) v = staged(sl, j, c);
-            Xre[(sl * ndk + c) * xs + j] = S(v.re);
-            Xim[(sl * ndk + c) * xs + j] = S(v.im);
-        }
+    } else if (wv == 0 && lane < nr) {
+        put_factor(lane, f0);
     }
+    auto block = [&](int sl) {
+        return sl < nself ? (self_mode == CS_SELF ? op.M + gs * 9 * nn : op.Minv + gs * nn) : op.M + (gs * 9 + 1 + sl - nself) * nn;
+    };
+    TileFrags<S, NS> f[MG == 1 ? 2 : MG];
+    TileFrags<S, NSI> fi;
+#pragma unroll
+    for (int u = 0; u < MG; u++)
+        if (grp + u * MG < ns) f[u].load(block(grp + u * MG), nd, r, q);
     __syncthreads();
-    const int w = t >> 6, lane = t & 63;
-    const int ntile = (nd + 15) / 16;
-    const int r = 16 * w + (lane & 15);
-    f32x4 cre = {0.f, 0.f, 0.f, 0.f}, cim = {0.f, 0.f, 0.f, 0.f};
-    if (w < ntile) {
-        auto sgn_of = [&](int sl) { return (sl >= nself && hop_sign < 0) ? -1.f : 1.f; };
-        if constexpr (NDK > 0) {
-            // software pipeline over the slots: block sl + 1 loads while block sl multiplies
-            TileFrags<S, NDK> fa, fb;
-            tile_load<S, NDK>(mat[0], nd, r, lane, sgn_of(0), fa);
-            for (int sl = 0; sl < ns; sl += 2) {
-                if (sl + 1 < ns) tile_load<S, NDK>(mat[sl + 1], nd, r, lane, sgn_of(sl + 1), fb);
-                tile_product<S, NDK>(fa, lane, Xre + sl * ndk * xs, Xim + sl * ndk * xs, xs, cre, cim);
-                if (sl + 1 >= ns) break;
-                if (sl + 2 < ns) tile_load<S, NDK>(mat[sl + 2], nd, r, lane, sgn_of(sl + 2), fa);
-                tile_product<S, NDK>(fb, lane, Xre + (sl + 1) * ndk * xs, Xim + (sl + 1) * ndk * xs, xs, cre, cim);
-            }
+    // body(slot, RHS, row, value) over the wave's entries
+    auto staged = [&](auto&& body) {
+        auto one = [&](int sl, int e, cx<float> val) {
+            if (e >= xs * NDK) return;
+            const int k = e / NDK;
+            body(sl, k, e - k * NDK, fac[sl >= nself][k] * val);
+        };
+#pragma unroll
+        for (int a = 0; a < PS; a++)
+            if (wv + a * nw < ns)
+#pragma unroll
+                for (int u = 0; u < SR; u++) one(wv + a * nw, lane + 64 * u, pre[a][u]);
+        for (int sl = wv; sl < ns; sl += nw) {   // what was not asked for ahead
+            const int e0 = sl < wv + PS * nw ? 64 * SR : 0;
+            if (e0 >= xs * NDK) continue;
+            const cx<float>* v = input(sl);
+            for (int e = lane + e0; e < xs * NDK; e += 64) one(sl, e, entry(v, e));
+        }
+    };
+    // FP16 form: column k of every slot is divided by sc[k], the largest modulus
+    // of the column's reals over the slots, so that the rounded inputs lie in
+    // [-1, 1] whatever the vector's magnitude; the products are scaled back in FP32
+    if constexpr (F16) {
+        staged([&](int, int k, int, cx<float> v) {
+            const float m = fmaxf(fabsf(v.re), fabsf(v.im));
+            if (m > 0.f) atomicMax(reinterpret_cast<int*>(sc) + k, __float_as_int(m));
+        });
+        __syncthreads();
+    }
+    staged([&](int sl, int k, int c, cx<float> v) {
+        float s = 1.f;
+        if constexpr (F16) s = sc[k] > 0.f ? 1.f / sc[k] : 0.f;
+        S* o = X + (sl * NDK + c) * cols + k;
+        o[0] = F16 ? S(v.re * s) : S(v.re);
+        o[xs] = F16 ? S(v.im * s) : S(v.im);
+    });
+    __syncthreads();
+    f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
+    // MG = 1 sums every slot from zero: chains of 2 nd products, not 18 nd, round
+    // less (the groups of MG = 3 cut them as well)
+    auto multiply = [&](const TileFrags<S, NS>& a, int sl) {
+        const S* x = X + sl * NDK * cols;
+        if constexpr (MG == 1) {
+            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+            a.template multiply<PACK>(x, xs, lane, s0, s1);
+            c0 += s0;
+            c1 += s1;
         } else {
-            for (int sl = 0; sl < ns; sl++)
-                tile_mma<S>(mat[sl], nd, ndk, r, lane, sgn_of(sl), Xre + sl * ndk * xs, Xim + sl * ndk * xs, xs, cre, cim);
+            a.template multiply<PACK>(x, xs, lane, c0, c1);
+        }
+    };
+    auto load_inverse = [&]() {
+        if (post_inv) fi.load(op.Minv + gs * nn, nd, r, q, grp, MG);
+    };
+    if constexpr (MG == 1) {
+        // block sl + 1 loads while block sl multiplies
+        for (int sl = 0; sl < ns; sl += 2) {
+            if (sl + 1 < ns) f[1].load(block(sl + 1), nd, r, q);
+            multiply(f[0], sl);
+            if (sl + 1 >= ns) break;
+            if (sl + 2 < ns) f[0].load(block(sl + 2), nd, r, q);
+            multiply(f[1], sl + 1);
+        }
+        load_inverse();
+    } else {
+#pragma unroll
+        for (int u = 0; u < MG; u++) {
+            if (grp + u * MG < ns) multiply(f[u], grp + u * MG);
+            if (u == 0) load_inverse();   // into the first slot's registers
         }
     }
-    // result rows 16w + 4q + v, column j
-    const int q = lane >> 4, j = lane & 15;
-    const bool jon = j < nr && mk.on(j);
-    if constexpr (F16) {
+    // the groups' partial tiles, added in order by group 0
+    auto meet = [&]() {
+        if constexpr (MG == 1) {
+            __syncthreads();
+            return;
+        }
+        if (grp) {
+            f32x4* o = red + ((grp - 1) * ntile + w) * (PACK ? 1 : 2) * 64 + lane;
+            o[0] = c0;
+            if constexpr (!PACK) o[64] = c1;
+        }
+        __syncthreads();
+        if (grp == 0)
+            for (int u = 1; u < MG; u++) {
+                const f32x4* o = red + ((u - 1) * ntile + w) * (PACK ? 1 : 2) * 64 + lane;
+                c0 += o[0];
+                if constexpr (!PACK) c1 += o[64];
+            }
+    };
+    meet();
+    // the lane's column: RHS k, real part (and in c1, or in lane + xs, the imaginary one)
+    const int k = PACK ? (j & (xs - 1)) : j;
+    const bool have = grp == 0 && (PACK ? j < cols : true);
+    if (grp == 0) {
+        if constexpr (F16) {
+            c0 *= sc[k];
+            c1 *= sc[k];
+        }
+        if (self_mode == CS_IDENT && have && k < nr && ((on >> k) & 1u)) {
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                const int row = 16 * w + 4 * q + v;
+                if (row < nd) {
+                    const cx<float> a = fac[0][k] * in1[(size_t)k * ld + gs * nd + row];
+                    c0[v] += (PACK && j >= xs) ? a.im : a.re;
+                    if constexpr (!PACK) c1[v] += a.im;
+                }
+            }
+        }
+    }
+    auto store = [&]() {
+        if (grp) return;
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-            cre[v] *= sc[j];
-            cim[v] *= sc[j];
+            const float im = PACK ? __shfl(c0[v], lane + xs, 64) : c1[v];
+            const int row = 16 * w + 4 * q + v;
+            if (j < xs && k < nr && ((on >> k) & 1u) && row < nd)
+                out[(size_t)k * ld + gs * nd + row] = cx<float>{c0[v], im};
         }
+    };
+    if (!post_inv) {
+        store();
+        return;
     }
-    if (self_mode == CS_IDENT && w < ntile && jon) {
+    // post multiplication by the self-block inverse: the result is the new X
+    // (zero rows up to the last step; FP16 form scaled per column as above)
+    for (int e = nd * cols + t; e < max(NS, NSI * MG) * K * cols; e += nt) X[e] = S(0.f);
+    float s = 1.f;
+    if constexpr (F16) {
+        __syncthreads();
+        if (t < 16) sc[t] = 0.f;
+        __syncthreads();
+        if (have) {
+            float m = 0.f;
+#pragma unroll
+            for (int v = 0; v < 4; v++)
+                if (16 * w + 4 * q + v < nd) m = fmaxf(m, PACK ? fabsf(c0[v]) : fmaxf(fabsf(c0[v]), fabsf(c1[v])));
+            if (m > 0.f) atomicMax(reinterpret_cast<int*>(sc) + k, __float_as_int(m));
+        }
+        __syncthreads();
+        s = sc[k] > 0.f ? 1.f / sc[k] : 0.f;
+    }
+    if (have)
 #pragma unroll
         for (int v = 0; v < 4; v++) {
             const int row = 16 * w + 4 * q + v;
             if (row < nd) {
-                const cx<float> a = fac[0][j] * in1[(size_t)j * ld + gs * nd + row];
-                cre[v] += a.re;
-                cim[v] += a.im;
+                X[row * cols + j] = F16 ? S(c0[v] * s) : S(c0[v]);
+                if constexpr (!PACK) X[row * cols + xs + j] = F16 ? S(c1[v] * s) : S(c1[v]);
             }
         }
-    }
-    if (!post_inv) {
-        if (w < ntile && jon) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int row = 16 * w + 4 * q + v;
-                if (row < nd) out[(size_t)j * ld + gs * nd + row] = cx<float>{cre[v], cim[v]};
-            }
-        }
-        return;
-    }
-    // post multiplication by the self-block inverse: stage the result as a new X
-    // (FP16 form: scaled per column as above)
     __syncthreads();
-    for (int e = t; e < ndk * xs; e += nt) {   // clear (padding rows stay zero)
-        Xre[e] = S(0.f);
-        Xim[e] = S(0.f);
-    }
+    c0 = f32x4{0.f, 0.f, 0.f, 0.f};
+    c1 = c0;
+    fi.template multiply<PACK>(X, xs, lane, c0, c1, grp, MG);
+    meet();
     if constexpr (F16) {
-        if (t < 16) sc[t] = 0.f;
-        __syncthreads();
-        if (w < ntile) {
-            float m = 0.f;
-#pragma unroll
-            for (int v = 0; v < 4; v++)
-                if (16 * w + 4 * q + v < nd) m = fmaxf(m, fmaxf(fabsf(cre[v]), fabsf(cim[v])));
-            if (m > 0.f) atomicMax(reinterpret_cast<int*>(sc) + j, __float_as_int(m));
-        }
+        c0 *= sc[k];
+        c1 *= sc[k];
     }
-    __syncthreads();
-    float inv = 1.f;
-    if constexpr (F16) inv = sc[j] > 0.f ? 1.f / sc[j] : 0.f;
-    if (w < ntile) {
-#pragma unroll
-        for (int v = 0; v < 4; v++) {
-            const int row = 16 * w + 4 * q + v;
-            if (row < nd && j < xs) {
-                Xre[row * xs + j] = S(cre[v] * inv);
-                Xim[row * xs + j] = S(cim[v] * inv);
-            }
-        }
-    }
-    __syncthreads();
-    if (w < ntile) {
-        f32x4 dre = {0.f, 0.f, 0.f, 0.f}, dim = {0.f, 0.f, 0.f, 0.f};
-        tile_any<S, NDK>(op.Minv + gs * nn, nd, ndk, r, lane, 1.f, Xre, Xim, xs, dre, dim);
-        if constexpr (F16) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                dre[v] *= sc[j];
-                dim[v] *= sc[j];
-            }
-        }
-        if (jon) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int row = 16 * w + 4 * q + v;
-                if (row < nd) out[(size_t)j * ld + gs * nd + row] = cx<float>{dre[v], dim[v]};
-            }
-        }
-    }
+    store();
 }
 
+template <class S, int NS, bool PACK, int ND, int MG>
+static void mfma_go(const CoarseOp<float, S>& op, int nsite, int par, int self_mode, const cx<float>* in1, int hop_sign,
+                    const cx<float>* in2, bool post_inv, cx<float>* out, hipStream_t s, Mask mk, int nr, long ld, InScale isc) {
+    const int ntile = (op.nd + 15) / 16;
+    // the inverse's steps are dealt round robin: its last ones may lie past NDK
+    const int rows = std::max(9 * NS, (NS + MG - 1) / MG * MG) * MfmaK<S>::K;
+    const size_t lds = sizeof(S) * rows * 2 * mfma_cols(nr) + sizeof(f32x4) * (MG - 1) * ntile * (PACK ? 1 : 2) * 64;
+    static std::mutex mu;
+    static size_t configured = 65536;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (lds > configured && hipFuncSetAttribute((const void*)k_coarse_apply_mfma<S, NS, PACK, ND, MG>,
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess)
+            configured = lds;
+    }
+    k_coarse_apply_mfma<S, NS, PACK, ND, MG><<<nsite + (isc.npart ? nr : 0), 64 * MG * ntile, lds, s>>>(
+        op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr, isc, nsite);
+}
+
+// instruction steps of a block column, rounded up to the compiled forms
+// (40 unknowns, N = 20, take their own)
 template <class S>
-static size_t mfma_lds_bytes(int nd, int nr) {
-    const int K = MfmaK<S>::K;
-    const int ndk = (nd + K - 1) / K * K;
-    return 2 * sizeof(S) * 9 * (size_t)ndk * mfma_cols(nr);
+static void mfma_launch(const CoarseOp<float, S>& op, int nsite, int par, int self_mode, const cx<float>* in1, int hop_sign,
+                        const cx<float>* in2, bool post_inv, cx<float>* out, hipStream_t s, Mask mk, int nr, long ld,
+                        InScale isc) {
+    auto pick = [&](auto ns) {
+        constexpr int NS = decltype(ns)::value;
+        auto go = [&](auto pack, auto n) {
+            constexpr bool P = decltype(pack)::value;
+            constexpr int ND = decltype(n)::value;
+            if (nsite < 1024) mfma_go<S, NS, P, ND, 3>(op, nsite, par, self_mode, in1, hop_sign, in2, post_inv, out, s, mk, nr, ld, isc);
+            else mfma_go<S, NS, P, ND, 1>(op, nsite, par, self_mode, in1, hop_sign, in2, post_inv, out, s, mk, nr, ld, isc);
+        };
+        constexpr std::integral_constant<int, 0> any{};
+        if constexpr (NS * MfmaK<S>::K == 40 || NS * MfmaK<S>::K == 48)
+            if (op.nd == 40 && nr <= 8) return go(std::true_type{}, std::integral_constant<int, 40>{});
+        if (nr <= 8) go(std::true_type{}, any);
+        else go(std::false_type{}, any);
+    };
+    const int steps = (op.nd + MfmaK<S>::K - 1) / MfmaK<S>::K;
+    if constexpr (std::is_same<S, float>::value) {
+        if (steps <= 5) pick(std::integral_constant<int, 5>{});
+        else if (steps <= 8) pick(std::integral_constant<int, 8>{});
+        else if (steps <= 10) pick(std::integral_constant<int, 10>{});
+        else if (steps <= 12) pick(std::integral_constant<int, 12>{});
+        else pick(std::integral_constant<int, 16>{});
+    } else {
+        if (steps <= 2) pick(std::integral_constant<int, 2>{});
+        else if (steps <= 3) pick(std::integral_constant<int, 3>{});
+        else pick(std::integral_constant<int, 4>{});
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -669,15 +727,7 @@ void coarse_apply(const CoarseOp<T, S>& op, int par, int self_mode, const cx<T>*
     if constexpr (std::is_same<T, float>::value) {
         // the matrix-core form serves FP32 arithmetic with 2..16 right-hand sides and nd <= 64
         if (op.mfma && nr >= 2 && nr <= 16 && op.nd <= 64) {
-            constexpr int K = MfmaK<S>::K;
-            constexpr int NDK40 = (40 + K - 1) / K * K;
-            const int extra = isc.npart ? nr : 0;
-            if (op.nd == 40)
-                k_coarse_apply_mfma<S, NDK40><<<nsite + extra, 64 * 3, mfma_lds_bytes<S>(op.nd, nr), s>>>(
-                    op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr, isc, nsite);
-            else
-                k_coarse_apply_mfma<S><<<nsite + extra, 64 * ((op.nd + 15) / 16), mfma_lds_bytes<S>(op.nd, nr), s>>>(
-                    op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, nr, isc, nsite);
+            mfma_launch<S>(op, nsite, par, self_mode, in1, hop_sign, in2, post_inv, out, s, mk, nr, ld, isc);
             return;
         }
     }
