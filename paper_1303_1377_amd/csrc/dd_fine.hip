@@ -12,6 +12,7 @@
 // packed clover blocks [parity][72][vh] reals.  One thread owns one site, so
 // every load of a component is coalesced across the wavefront.
 #include <mutex>
+#include <type_traits>
 
 #include "dd_kernels.h"
 
@@ -715,19 +716,26 @@ void fine_dirac_from32(const FineOp<double>& op, const cx<float>* in, cx<double>
 // lanes per pair of block sites (the even and the odd site of one local layout
 // index), each lane holding one chirality half of both.  With r = b - D z
 // restricted to the block and H the hopping part of D:
-//   t0_e = A_e^{-1}(b_e - (H z)_e) - z_e               (= A_ee^{-1} r_e)
-//   f_o  = b_o - A_o z_o - (H z)_o - (H_int t0)_o        (= r_o - D_oe A_ee^{-1} r_e)
+//   z_e <- A_e^{-1}(b_e - (H z)_e)                       (= z_e + t0, t0 = A_ee^{-1} r_e)
+//   f_o  = b_o - A_o z_o - (H z)_o  with the new z_e     (= r_o - D_oe A_ee^{-1} r_e)
 //   MR on S = A_oo - D_oe A_ee^{-1} D_eo (block-internal hops) from e_o = 0
-//   e_e  = t0_e - A_e^{-1} (H_int e_o)_e
-//   z   += e on the block
+//   z_e -= A_e^{-1} (H_int e_o)_e,  z_o += e_o
 // The block's operator stays on chip for the whole half sweep: the links
 // joining two sites of the block live in LDS as their first two rows (the
 // third row of an SU(3) matrix is conj(row0 x row1)), each lane keeps its
 // chirality half of the clover blocks (A^{-1} at the even, A at the odd site)
 // in registers, and the block fields E (even) and O (odd) are exchanged
-// through LDS.  Every
-// link, clover entry and spinor is therefore read from memory once per half
-// sweep.  The MR inner products are wavefront shuffles plus one LDS step.
+// through LDS.  The MR inner products are wave sums plus one LDS step.
+//
+// The residual b - H z splits its hops.  Those inside the block run like the MR
+// steps' over z staged in the block fields.  Those that leave it (a quarter of
+// all hops for 4^4 blocks) are dealt evenly to the lanes, one (side, face site,
+// spin) each per direction, and added to b in the block fields first.  Walking the
+// eight hops of a site with every lane gathering cost one memory round trip per
+// hop at two waves per SIMD (1285 of 1985 us), and -H_int t0 another sum.  Half
+// sweep, 64x32^3, FP32, 4 RHS: 863 us + 187 us per MR step, the latter at the
+// issue rate of the vector unit; with 4 MR steps 1985 -> 1608 us.  16^4, 3 MR
+// steps: FP64 57.4 -> 54.1 us, FP32 52.5 -> 42.4 us.
 // ---------------------------------------------------------------------------
 struct LinkMap {        // compact index of the block-internal links of direction mu
     int ext[4][4];      // box extents per direction
@@ -779,33 +787,125 @@ __device__ __forceinline__ void lds_store(cx<T>* buf, int bvh, int l, const cx<T
     for (int c = 0; c < 12; c++) buf[c * bvh + l] = v[c];
 }
 
-// hop k of the lane's own site (p, i) for the block residual.  tab[k][t]
-// packs, for a hop inside the block, the LDS slot of the link (<< 8) and the
-// neighbour's local index; -1 marks a hop that leaves the block (its link is
-// read from memory).  The neighbour spinor comes from global memory psi.
-template <class T, class S, class VP>
-__device__ __forceinline__ void sap_hop(const FineOp<T, S>& op, int ltot, const cx<T>* __restrict__ L,
-                                        const int* __restrict__ tab, int ntab, int k, int t, int p, int i,
-                                        const int x[4], int base, const VP& psi, cx<T> acc[12]) {
-    const Geom& g = op.g;
-    const int code = tab[k * ntab + t];
-    const int mu = k & 3;
-    const bool fwd = k < 4;
-    const int j = (code >= 0) ? base + (code & 255) : nb_index_sel(g, x, k);
-    cx<T> v[12], u[9], h[6], gg[6];
-    load_spinor(psi, g.vh, 1 - p, j, v);
-    if (code >= 0) {
-        const int li = code >> 8;
+// Hops that leave the block in direction MU, over its two faces: 2 n of them for
+// faces of n sites (none where one block spans the direction).  Two lanes share a
+// hop, one per spin s of the projected two-spinor: lane e takes spin e / 2n of hop
+// e mod 2n.  Hops run forward, then backward; within a face by parity, then by
+// local index, so that neighbouring lanes read neighbouring entries.
+struct FaceLane {
+    int j;      // layout index of the neighbour
+    int code;   // local index of the block site | its parity << 8 | backward << 9 | s << 10; no hop: -1
+};
+__device__ __forceinline__ int face_lanes(const Geom& g, int mu) { return g.nb[mu] == 1 ? 0 : (8 * g.bvh) >> g.lb[mu]; }
+
+template <int MU>
+__device__ __forceinline__ FaceLane face_lane(const Geom& g, const int x0[4], int e) {
+    const int n = face_lanes(g, MU) >> 1, face = n >> 1, par = face >> 1;
+    FaceLane f{0, -1};
+    if (e >= 2 * n) return f;
+    const int s = e >= n;
+    int q = e - s * n;
+    const int back = q >= face;
+    q -= back * face;
+    const int p = q >= par;
+    q -= p * par;
+    // the fastest of the other directions counts in steps of two; its low bit follows from the parity
+    constexpr int fast = MU == 3 ? 2 : 3;
+    int lc[4];
+    lc[MU] = back ? 0 : g.b[MU] - 1;
+    int sum = lc[MU];
 #pragma unroll
-        for (int e = 0; e < 6; e++) u[e] = L[e * ltot + li];
-        su3_rebuild(u);
-    } else {
-        load_link(op, fwd ? p : 1 - p, mu, fwd ? i : j, u);
+    for (int nu = 3; nu >= 0; nu--) {
+        if (nu == MU) continue;
+        const int lb = g.lb[nu] - (nu == fast ? 1 : 0);
+        const int v = q & ((1 << lb) - 1);
+        q >>= lb;
+        lc[nu] = nu == fast ? 2 * v : v;
+        sum += lc[nu];
     }
-    const T sgn = fwd ? T(-1) : T(1);
-    spin_project(mu, sgn, v, h);
-    su3_two_spinor(u, !fwd, h, gg);
-    spin_reconstruct(mu, sgn, gg, acc);
+    lc[fast] += (p + sum) & 1;
+    const int l = ((((lc[0] << g.lb[1] | lc[1]) << g.lb[2] | lc[2]) << g.lb[3]) | lc[3]) >> 1;
+    int x[4];
+#pragma unroll
+    for (int nu = 0; nu < 4; nu++) x[nu] = x0[nu] + lc[nu];
+    f.j = nb_index_sel(g, x, MU + 4 * back);
+    f.code = l | p << 8 | back << 9 | s << 10;
+    return f;
+}
+
+// one spin (0..3) of a site
+template <class T>
+__device__ __forceinline__ void spin_load(const cx<T>* psi, int vh, int p, int spin, int i, cx<T> v[3]) {
+    const cx<T>* base = psi + (size_t)(p * 12 + 3 * spin) * vh + i;
+#pragma unroll
+    for (int c = 0; c < 3; c++) v[c] = base[(size_t)c * vh];
+}
+template <class T>
+__device__ __forceinline__ void spin_load(const hspin& psi, int vh, int p, int spin, int i, cx<T> v[3]) {
+    const hpair* base = psi.d + (size_t)((2 * p + (spin >> 1)) * 7) * vh + i;
+    const float sc = __builtin_bit_cast(float, base[(size_t)6 * vh]);
+    const int c0 = 3 * (spin & 1);
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const hpair q = base[(size_t)(c0 + c) * vh];
+        v[c] = {T((float)q.x * sc), T((float)q.y * sc)};
+    }
+}
+
+// upper spin s, the lower spin that B_MU pairs with it, and the link of a hop
+// (backward: transposed; face_add conjugates it)
+template <class T>
+struct FaceData {
+    cx<T> up[3], lo[3], u[9];
+};
+template <int MU>
+__device__ __forceinline__ int face_lower(int s) { return MU < 2 ? 1 - s : s; }
+// (lanes without a hop read entry 0 of the field and add nothing: no branch around the loads)
+template <int MU, class T, class S, class VP>
+__device__ __forceinline__ void face_load(const FineOp<T, S>& op, const FaceLane& f, int base, const VP& psi, FaceData<T>& d) {
+    const int code = f.code < 0 ? 0 : f.code;
+    const int p = (code >> 8) & 1, back = (code >> 9) & 1, s = (code >> 10) & 1;
+    const size_t vh = op.g.vh;
+    spin_load(psi, op.g.vh, 1 - p, s, f.j, d.up);
+    spin_load(psi, op.g.vh, 1 - p, 2 + face_lower<MU>(s), f.j, d.lo);
+    const cx<S>* u = op.U + (size_t)((back ? 1 - p : p) * 4 + MU) * 9 * vh + (back ? f.j : base + (code & 255));
+    const size_t row = back ? vh : 3 * vh, col = back ? 3 * vh : vh;
+#pragma unroll
+    for (int a = 0; a < 3; a++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) d.u[a * 3 + c] = ccast<T>(u[a * row + c * col]);
+}
+
+// field += 1/2 of the lane's part of the hop: with h = up + sg c lo (sg = -1
+// forward, +1 backward; c = i | -+1 | +-i | 1 for MU = 0..3, upper sign for s = 0)
+// and g = U h (U^H h backward), spin s takes g and its lower spin sg conj(c) g
+template <int MU, class T>
+__device__ __forceinline__ void face_add(const FaceLane& f, int bvh, cx<T>* E, cx<T>* O, const FaceData<T>& d) {
+    const int s = (f.code >> 10) & 1;
+    const T sg = (f.code >> 9) & 1 ? T(1) : T(-1);
+    const T k = MU == 1 ? (s ? sg : -sg) : MU == 2 ? (s ? -sg : sg) : sg;
+    cx<T> h[3], gg[3];
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        if (MU == 0 || MU == 2) h[c] = {d.up[c].re - k * d.lo[c].im, d.up[c].im + k * d.lo[c].re};
+        else h[c] = {d.up[c].re + k * d.lo[c].re, d.up[c].im + k * d.lo[c].im};
+    }
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        gg[a] = czero<T>();
+#pragma unroll
+        for (int c = 0; c < 3; c++) cmac(gg[a], cx<T>{d.u[a * 3 + c].re, -sg * d.u[a * 3 + c].im}, h[c]);
+    }
+    if (f.code < 0) return;
+    cx<T>* fld = ((f.code >> 8) & 1 ? O : E) + (f.code & 255);
+    cx<T>* fu = fld + 3 * s * bvh;
+    cx<T>* fl = fld + (6 + 3 * face_lower<MU>(s)) * bvh;
+    const T hk = T(0.5) * k;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        fu[a * bvh] += T(0.5) * gg[a];
+        fl[a * bvh] += (MU == 0 || MU == 2) ? cx<T>{hk * gg[a].im, -hk * gg[a].re} : hk * gg[a];
+    }
 }
 
 // value of the partner lane (lane ^ 1): DPP quad permutation [1, 0, 3, 2]
@@ -908,7 +1008,9 @@ __device__ __forceinline__ void pair_hop(const cx<T>* __restrict__ L, int ltot, 
 
 // MINW: waves per SIMD the register allocation must allow (2 for FP32 fields,
 // so that two workgroups share a CU; FP64 needs the whole register file)
-template <class T, class S, class VP, int MINW = (sizeof(T) > 4 ? 1 : 2)>
+// THIN: some direction has more hops out of the block than the workgroup lanes
+// (extent two beside longer ones)
+template <class T, class S, class VP, bool THIN, int MINW = (sizeof(T) > 4 ? 1 : 2)>
 __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const int* __restrict__ blocks, VP b0, VP z0,
                                                   int mr_steps, int nr, long ld, Mask mk) {
     extern __shared__ char smem_raw[];
@@ -1002,50 +1104,84 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
             R[c] = {keep.re + pair_swap(snd[c].re), keep.im + pair_swap(snd[c].im)};
         }
     };
+    // the lane's hops out of the block, one per direction (thin blocks have more)
+    int x0[4];
+    cb_coords(g, 0, base, x0);
+#pragma unroll
+    for (int mu = 0; mu < 4; mu++) x0[mu] &= ~(g.b[mu] - 1);
+    FaceLane f0 = face_lane<0>(g, x0, t), f1 = face_lane<1>(g, x0, t), f2 = face_lane<2>(g, x0, t), f3 = face_lane<3>(g, x0, t);
     for (int rhs = 0; rhs < nr; rhs++) {
     if (!mk.on(rhs)) continue;
     const typename vrestrict<VP>::type b = b0 + rhs * ld;
     const typename vrestrict<VP>::type z = z0 + rhs * ld;
     // half h of: e_o, rho (the odd MR residual), w, R
     cx<T> eo[6], rho[6], w[6], R[6];
-    // ---- residual on the block, b - H z with all 8 hops of the lane's own site ----
-    if (act) {
-        cx<T> acc[12], v[12];
-#pragma unroll
-        for (int c = 0; c < 12; c++) acc[c] = czero<T>();
-#pragma unroll 1
-        for (int k = 0; k < 8; k++) sap_hop<T, S>(op, ltot, L, tab, ntab, k, sidx, h, i, x, base, z, acc);
-        load_spinor(b, g.vh, h, i, v);
-#pragma unroll
-        for (int c = 0; c < 12; c++) v[c] += T(0.5) * acc[c];
-        lds_store(h ? O : E, bvh, l, v);
-    }
-    __syncthreads();
-    if (act) {
-        cx<T> vh6[6], zh[6], t0[6];
-        // t0_e = A_e^{-1} (b - H z)_e - z_e
-        lds_load6(E, bvh, h, l, vh6);
-        half_load(z, g.vh, 0, h, i, zh);
-        herm6_apply(me, vh6, t0);
-#pragma unroll
-        for (int c = 0; c < 6; c++) {
-            t0[c] -= zh[c];
-            zh[c] += t0[c];
+    // ---- residual on the block, b - H z ----
+    // b and the hops that leave the block, in the block fields, direction by
+    // direction: a site on several faces is added to by one lane at a time.  The
+    // next direction's gathers are in flight while one is added.
+    {
+        // opaque per right-hand side: keeps the compiler from hoisting the links and
+        // all their addresses out of the loop (they would not fit in registers)
+        asm volatile("" : "+v"(f0.j), "+v"(f0.code), "+v"(f1.j), "+v"(f1.code), "+v"(f2.j), "+v"(f2.code), "+v"(f3.j),
+                          "+v"(f3.code));
+        FaceData<T> da, db;
+        face_load<0>(op, f0, base, z, da);
+        if (act) {
+            cx<T> v[12];
+            load_spinor(b, g.vh, h, i, v);
+            lds_store(h ? O : E, bvh, l, v);
         }
-        // z_e + t0 now (the block's z has been read by all its lanes), the
-        // rest of e_e after the MR steps: t0 need not stay in registers
-        half_store(z, g.vh, 0, h, i, zh);
-        // r_o = (b - H z)_o - A_o z_o
-        lds_load6(O, bvh, h, l, vh6);
+        face_load<1>(op, f1, base, z, db);
+        __syncthreads();
+        face_add<0>(f0, bvh, E, O, da);
+        face_load<2>(op, f2, base, z, da);
+        __syncthreads();
+        face_add<1>(f1, bvh, E, O, db);
+        face_load<3>(op, f3, base, z, db);
+        __syncthreads();
+        face_add<2>(f2, bvh, E, O, da);
+        __syncthreads();
+        face_add<3>(f3, bvh, E, O, db);
+        __syncthreads();
+        auto more = [&](auto mu) {
+            constexpr int MU = decltype(mu)::value;
+            if (!THIN || face_lanes(g, MU) <= (int)blockDim.x) return;
+            const FaceLane f = face_lane<MU>(g, x0, t + (int)blockDim.x);
+            face_load<MU>(op, f, base, z, da);
+            face_add<MU>(f, bvh, E, O, da);
+            __syncthreads();
+        };
+        more(std::integral_constant<int, 0>{});
+        more(std::integral_constant<int, 1>{});
+        more(std::integral_constant<int, 2>{});
+        more(std::integral_constant<int, 3>{});
+    }
+    if (act) {
+        cx<T> zh[6];
         half_load(z, g.vh, 1, h, i, zh);
-        herm6_apply(mo, zh, w);
-#pragma unroll
-        for (int c = 0; c < 6; c++) rho[c] = vh6[c] - w[c];
-        lds_store6(E, bvh, h, l, t0);  // each lane overwrites only the half it read
+        lds_load6(O, bvh, h, l, rho);
+        lds_store6(O, bvh, h, l, zh);   // each lane overwrites only the half it read
     }
     __syncthreads();
     if (act) {
-        // rho = f_o = r_o - D_oe t0, e_o = 0
+        // z_e + t0 = A_e^{-1} (b - H z)_e: stored now, the rest of e_e after the MR
+        // steps, and the inner hops of r_o - D_oe t0 run over it
+        pair_hops(0, O, R);
+        lds_load6(E, bvh, h, l, w);
+#pragma unroll
+        for (int c = 0; c < 6; c++) w[c] += T(0.5) * R[c];
+        herm6_apply(me, w, eo);
+        half_store(z, g.vh, 0, h, i, eo);
+        lds_store6(E, bvh, h, l, eo);
+        lds_load6(O, bvh, h, l, eo);
+        herm6_apply(mo, eo, w);
+#pragma unroll
+        for (int c = 0; c < 6; c++) rho[c] -= w[c];
+    }
+    __syncthreads();
+    if (act) {
+        // rho = f_o = r_o - D_oe t0 (the inner hops of both from z_e + t0), e_o = 0
         pair_hops(1, E, R);
 #pragma unroll
         for (int c = 0; c < 6; c++) {
@@ -1106,7 +1242,7 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
         if (act) lds_store6(O, bvh, h, l, eo);
         __syncthreads();
     }
-    // ---- back-substitution and update: e_e = t0 - A_e^{-1} (H_int e_o)_e, t0 already in z ----
+    // ---- back-substitution and update: z_e + t0 is in z already ----
     if (act) {
         pair_hops(0, O, R);
 #pragma unroll
@@ -1135,11 +1271,9 @@ size_t fine_sap_lds_bytes(const Geom& g) {
            3 * sizeof(double) * (nt / 64);
 }
 
-template <class T, class S, class VP>
-static void sap_launch(const FineOp<T, S>& op, const int* blocks, int nblocks, VP b, VP z, int mr_steps, hipStream_t s,
-                       int nr, long ld, Mask mk) {
-    if (nblocks <= 0) return;
-    int nt = ((2 * op.g.bvh + 63) / 64) * 64;
+template <class T, class S, class VP, bool THIN>
+static void sap_go(const FineOp<T, S>& op, const int* blocks, int nblocks, int nt, VP b, VP z, int mr_steps, hipStream_t s,
+                   int nr, long ld, Mask mk) {
     size_t lds = fine_sap_lds_bytes<T>(op.g);
     static std::mutex mu;
     static size_t configured = 0;
@@ -1147,11 +1281,22 @@ static void sap_launch(const FineOp<T, S>& op, const int* blocks, int nblocks, V
         std::lock_guard<std::mutex> lock(mu);
         // a refusal leaves its error for the launch below to report
         if (lds > 65536 && lds > configured &&
-            hipFuncSetAttribute((const void*)k_sap_fine<T, S, VP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)k_sap_fine<T, S, VP, THIN>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) == hipSuccess)
             configured = lds;
     }
-    k_sap_fine<T, S, VP><<<nblocks, nt, lds, s>>>(op, blocks, b, z, mr_steps, nr, ld, mk);
+    k_sap_fine<T, S, VP, THIN><<<nblocks, nt, lds, s>>>(op, blocks, b, z, mr_steps, nr, ld, mk);
+}
+
+template <class T, class S, class VP>
+static void sap_launch(const FineOp<T, S>& op, const int* blocks, int nblocks, VP b, VP z, int mr_steps, hipStream_t s,
+                       int nr, long ld, Mask mk) {
+    if (nblocks <= 0) return;
+    const int nt = ((2 * op.g.bvh + 63) / 64) * 64;
+    bool thin = false;
+    for (int mu = 0; mu < 4; mu++) thin = thin || (op.g.nb[mu] != 1 && ((8 * op.g.bvh) >> op.g.lb[mu]) > nt);
+    if (thin) sap_go<T, S, VP, true>(op, blocks, nblocks, nt, b, z, mr_steps, s, nr, ld, mk);
+    else sap_go<T, S, VP, false>(op, blocks, nblocks, nt, b, z, mr_steps, s, nr, ld, mk);
 }
 
 template <class T, class S>
