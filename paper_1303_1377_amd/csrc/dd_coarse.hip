@@ -1682,79 +1682,84 @@ __device__ __forceinline__ void agg_site_c(const AggMap& m, const int xc[4], int
     x[3] = xc[3] * m.a[3] + l3;
 }
 
-// workgroup: coarser site; thread e < asz*ndf: (site s = e / ndf, row d = e % ndf)
-template <class T, class S>
-__global__ void k_coarse_restrict(AggMap m, int ndf, int N, const cx<S>* __restrict__ P, const cx<T>* __restrict__ in,
-                                  cx<T>* __restrict__ out, long ldi, long ldo, Mask mk) {
-    if (!mk.on(blockIdx.y)) return;
-    in += blockIdx.y * ldi;
-    out += blockIdx.y * ldo;
-    extern __shared__ char smem_raw[];
-    cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);
+// out_r[h N + k] = sum over half h of the aggregate's rows of conj(P_k) in_r, for a
+// group of KR right-hand sides.  Workgroup: coarser site (and a share of the test
+// vectors, grid.z); a wave takes every fourth test vector with all its loads in
+// flight, one per 64 rows, so a row of P is read once for the group and a sum
+// over the aggregate is one wave sum.  Four waves on each test vector in turn
+// waited for memory once per vector and RHS: 64x32^3 level 1 -> 2, N = 20, FP32,
+// four RHS 264 -> 56 us; 32x16^3, FP16 storage, one RHS 65 -> 13.5 us.
+static constexpr int CR_EPT = 16;   // rows per lane: an aggregate has at most 1024
+template <class T, class S, int KR>
+__global__ void __launch_bounds__(256) k_coarse_restrict(AggMap m, int ndf, int N, const cx<S>* __restrict__ P,
+                                                         const cx<T>* __restrict__ in, cx<T>* __restrict__ out, long ldi,
+                                                         long ldo, int nr, Mask mk) {
+    const int q0 = blockIdx.y * KR;
+    unsigned on = 0;
+#pragma unroll
+    for (int r = 0; r < KR; r++)
+        if (q0 + r < nr && mk.on(q0 + r)) on |= 1u << r;
+    if (!on) return;
+    extern __shared__ __align__(16) char smem_raw[];
+    cx<T>* v = reinterpret_cast<cx<T>*>(smem_raw);   // [KR][ne]
     const int gc = blockIdx.x;
     const int pc = gc >= m.c.vh, ic = gc - pc * m.c.vh;
     int xc[4];
     cb_coords(m.c, pc, ic, xc);
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = (blockDim.x + 63) >> 6;
-    const long volf = 2L * m.f.vh;
-    const int h0 = ndf / 2;
-    const int ne = m.asz * ndf;
-    // up to EPT entries per thread: their offsets, halves and input values are
-    // found once for all N test vectors (the same sums in the same order)
-    constexpr int EPT = 4;
-    const bool held = ne <= EPT * (int)blockDim.x;
-    size_t off[EPT];
-    cx<T> vin[EPT];
-    bool hi[EPT];
-    if (held) {
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const size_t volf = 2L * m.f.vh;
+    const int h0 = ndf / 2, ne = m.asz * ndf;
+    size_t off[CR_EPT];
+    unsigned upper = 0;   // bit u: the lane's row u lies in half 1
 #pragma unroll
-        for (int u = 0; u < EPT; u++) {
-            const int e = t + u * (int)blockDim.x;
-            off[u] = 0;
-            vin[u] = czero<T>();
-            hi[u] = false;
-            if (e < ne) {
-                const int s = e / ndf, d = e % ndf;
-                int x[4];
-                agg_site_c(m, xc, s, x);
-                off[u] = lay_global(m.f, x) * ndf + d;
-                vin[u] = in[off[u]];
-                hi[u] = d >= h0;
-            }
-        }
+    for (int u = 0; u < CR_EPT; u++) {
+        off[u] = 0;
+        if (64 * u >= ne) continue;
+        const int e = min(lane + 64 * u, ne - 1);
+        const int s = e / ndf, d = e - s * ndf;
+        int x[4];
+        agg_site_c(m, xc, s, x);
+        off[u] = lay_global(m.f, x) * ndf + d;
+        if (d >= h0) upper |= 1u << u;
     }
-    cx<double> acc[2];
-    for (int k = 0; k < N; k++) {
-        acc[0] = acc[1] = czero<double>();
-        if (held) {
-            const cx<S>* Pk = P + (size_t)k * volf * ndf;
+    // wave w stages the right-hand sides w, w + 4, ...
+    for (int r = w; r < KR; r += 4)
 #pragma unroll
-            for (int u = 0; u < EPT; u++) {
-                if (t + u * (int)blockDim.x >= ne) break;
-                const cx<double> pr = ccast<double>(cmulc(ccast<T>(Pk[off[u]]), vin[u]));
-                if (hi[u]) acc[1] += pr;
-                else acc[0] += pr;
-            }
-        } else {
-            for (int e = t; e < ne; e += blockDim.x) {
-                int s = e / ndf, d = e % ndf;
-                int x[4];
-                agg_site_c(m, xc, s, x);
-                size_t gf = lay_global(m.f, x);
-                acc[d / h0] += ccast<double>(cmulc(ccast<T>(P[((size_t)k * volf + gf) * ndf + d]), in[gf * ndf + d]));
-            }
+        for (int u = 0; u < CR_EPT; u++) {
+            const int e = lane + 64 * u;
+            if (e < ne) v[r * ne + e] = ((on >> r) & 1u) ? in[(size_t)(q0 + r) * ldi + off[u]] : czero<T>();
         }
-        for (int h = 0; h < 2; h++) {
-            acc[h].re = wave_sum(acc[h].re);
-            acc[h].im = wave_sum(acc[h].im);
-            if (lane == 0) red[w * 2 * N + h * N + k] = acc[h];
-        }
-    }
     __syncthreads();
-    for (int q = t; q < 2 * N; q += blockDim.x) {
-        cx<double> s = czero<double>();
-        for (int ww = 0; ww < nw; ww++) s += red[ww * 2 * N + q];
-        out[(size_t)gc * 2 * N + q] = ccast<T>(s);
+    for (int k = blockIdx.z * 4 + w; k < N; k += 4 * gridDim.z) {
+        const cx<S>* Pk = P + (size_t)k * volf * ndf;
+        cx<S> p[CR_EPT];
+#pragma unroll
+        for (int u = 0; u < CR_EPT; u++)
+            if (64 * u < ne) p[u] = Pk[off[u]];
+        cx<double> a0[KR], a1[KR];
+#pragma unroll
+        for (int r = 0; r < KR; r++) a0[r] = a1[r] = czero<double>();
+#pragma unroll
+        for (int u = 0; u < CR_EPT; u++) {
+            const int e = lane + 64 * u;
+            if (e >= ne) continue;
+            const cx<T> pu = ccast<T>(p[u]);
+#pragma unroll
+            for (int r = 0; r < KR; r++) {
+                const cx<double> pr = ccast<double>(cmulc(pu, v[r * ne + e]));
+                if ((upper >> u) & 1u) a1[r] += pr;
+                else a0[r] += pr;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < KR; r++) {
+            const cx<double> s0 = {wave_sum(a0[r].re), wave_sum(a0[r].im)}, s1 = {wave_sum(a1[r].re), wave_sum(a1[r].im)};
+            if (lane == 0 && ((on >> r) & 1u)) {
+                cx<T>* o = out + (size_t)(q0 + r) * ldo + (size_t)gc * 2 * N + k;
+                o[0] = ccast<T>(s0);
+                o[N] = ccast<T>(s1);
+            }
+        }
     }
 }
 
@@ -1782,10 +1787,18 @@ __global__ void k_coarse_prolong(AggMap m, int ndf, int N, const cx<S>* __restri
 template <class T, class S>
 void coarse_restrict(const AggMap& m, int ndf, int N, const cx<S>* P, const cx<T>* in, cx<T>* out, hipStream_t s,
                      int nr, long ldi, long ldo, Mask mk) {
-    int nt = 256;
-    size_t lds = sizeof(cx<double>) * 2 * N * (nt / 64);
-    dim3 grid(2 * m.c.vh, nr);
-    k_coarse_restrict<T, S><<<grid, nt, lds, s>>>(m, ndf, N, P, in, out, ldi, ldo, mk);
+    // the test vectors are split until about 512 workgroups run
+    const int ks = std::max(1, std::min((N + 3) / 4, 512 / std::max(1, 2 * m.c.vh)));
+    auto go = [&](auto kr) {
+        constexpr int KR = decltype(kr)::value;
+        dim3 grid(2 * m.c.vh, (nr + KR - 1) / KR, ks);
+        const size_t lds = sizeof(cx<T>) * KR * m.asz * ndf;
+        k_coarse_restrict<T, S, KR><<<grid, 256, lds, s>>>(m, ndf, N, P, in, out, ldi, ldo, nr, mk);
+    };
+    // (at most 32 KB of staged rows: 1024 rows of four FP32 or two FP64 vectors)
+    if (sizeof(T) == 4 && nr >= 3) go(std::integral_constant<int, 4>{});
+    else if (nr >= 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 1>{});
 }
 template <class T, class S>
 void coarse_prolong(const AggMap& m, int ndf, int N, const cx<S>* P, const cx<T>* in, cx<T>* out, hipStream_t s,
