@@ -38,32 +38,101 @@ __global__ void k_import_gauge(Geom g, const double* __restrict__ canon, cx<T>* 
         for (int e = 0; e < 9; e++) U[((size_t)(p * 4 + mu) * 9 + e) * g.vh + i] = ccast<T>(src[mu * 9 + e]);
 }
 
-template <class T>
-__global__ void k_import_vectors(Geom g, int n, const double* __restrict__ canon, cx<T>* __restrict__ out) {
-    long s = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    long vol = 2L * g.vh;
-    if (s >= vol) return;
-    int x[4];
-    canon_coords(g.d, s, x);
-    int p = site_parity(x), i = cb_index(g, x);
-    const cx<double>* src = reinterpret_cast<const cx<double>*>(canon);
-    for (int v = 0; v < n; v++)
-        for (int c = 0; c < 12; c++)
-            out[(size_t)v * 24 * g.vh + (size_t)(p * 12 + c) * g.vh + i] = ccast<T>(src[((size_t)v * vol + s) * 12 + c]);
+// Canonical spinors [site][12] to and from the layout [parity][12][vh].  A
+// workgroup takes whole layout blocks, LC_SITES sites: both sides then move
+// contiguous pieces (the canonical one a block's rows of x3, the layout one bvh
+// entries per component), and the transposition is in LDS.  One site per thread
+// wrote (read) 32-byte pieces of the layout.  64x32^3, four FP32 vectors: import
+// 640 -> 470 us, export 861 -> 451 us (5 TB/s).
+static constexpr int LC_SITES = 256;
+struct SiteSlot {
+    int canon;   // canonical site index, -1 past the lattice
+    int slot;    // place among the workgroup's sites in layout order (block, parity, local index)
+};
+// site q of the workgroup in (block, canonical order within the block)
+__device__ __forceinline__ SiteSlot site_slot(const Geom& g, int q) {
+    const int f = blockIdx.x * LC_SITES + q;
+    if (f >= 2 * g.vh) return SiteSlot{-1, q};
+    const int lex = f & (2 * g.bvh - 1);
+    int blk = f >> (g.lbvh + 1);
+    int r = lex, lc[4], x[4];
+#pragma unroll
+    for (int mu = 3; mu >= 0; mu--) {
+        lc[mu] = r & (g.b[mu] - 1);
+        r >>= g.lb[mu];
+    }
+#pragma unroll
+    for (int mu = 3; mu >= 0; mu--) {
+        const int n = mu ? blk % g.nb[mu] : blk;
+        if (mu) blk /= g.nb[mu];
+        x[mu] = (n << g.lb[mu]) + lc[mu];
+    }
+    const int p = (lc[0] + lc[1] + lc[2] + lc[3]) & 1;
+    return SiteSlot{(int)canon_index(g.d, x), (q & ~(2 * g.bvh - 1)) + p * g.bvh + (lex >> 1)};
+}
+// first component of the layout site in slot u
+__device__ __forceinline__ size_t slot_entry(const Geom& g, int u) {
+    const int f = blockIdx.x * LC_SITES + u;
+    const int p = (f >> g.lbvh) & 1, i = ((f >> (g.lbvh + 1)) << g.lbvh) + (f & (g.bvh - 1));
+    return (size_t)p * 12 * g.vh + i;
 }
 
 template <class T>
-__global__ void k_export_vectors(Geom g, int n, const cx<T>* __restrict__ in, double* __restrict__ canon) {
-    long s = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    long vol = 2L * g.vh;
-    if (s >= vol) return;
-    int x[4];
-    canon_coords(g.d, s, x);
-    int p = site_parity(x), i = cb_index(g, x);
-    cx<double>* dst = reinterpret_cast<cx<double>*>(canon);
-    for (int v = 0; v < n; v++)
-        for (int c = 0; c < 12; c++)
-            dst[((size_t)v * vol + s) * 12 + c] = ccast<double>(in[(size_t)v * 24 * g.vh + (size_t)(p * 12 + c) * g.vh + i]);
+__global__ void __launch_bounds__(LC_SITES) k_import_vectors(Geom g, int n, const double* __restrict__ canon, cx<T>* __restrict__ out) {
+    __shared__ SiteSlot ss[LC_SITES];
+    __shared__ cx<T> buf[LC_SITES * 13];
+    const int t = threadIdx.x;
+    ss[t] = site_slot(g, t);
+    __syncthreads();
+    const size_t v = blockIdx.y;
+    const cx<double>* src = reinterpret_cast<const cx<double>*>(canon) + v * 24 * g.vh;
+    cx<double> in[12];
+    int to[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = t + k * LC_SITES, q = e / 12, c = e - 12 * q;
+        const SiteSlot s = ss[q];
+        to[k] = s.slot * 13 + c;
+        in[k] = src[(size_t)max(s.canon, 0) * 12 + c];   // (no branch around the loads)
+    }
+#pragma unroll
+    for (int k = 0; k < 12; k++) buf[to[k]] = ccast<T>(in[k]);
+    __syncthreads();
+    if (blockIdx.x * LC_SITES + t >= 2 * g.vh) return;
+    cx<T>* o = out + v * 24 * g.vh + slot_entry(g, t);
+#pragma unroll
+    for (int c = 0; c < 12; c++) o[(size_t)c * g.vh] = buf[t * 13 + c];
+}
+
+template <class T>
+__global__ void __launch_bounds__(LC_SITES) k_export_vectors(Geom g, int n, const cx<T>* __restrict__ in, double* __restrict__ canon) {
+    __shared__ SiteSlot ss[LC_SITES];
+    __shared__ cx<T> buf[LC_SITES * 13];
+    const int t = threadIdx.x;
+    const size_t v = blockIdx.y;
+    if (blockIdx.x * LC_SITES + t < 2 * g.vh) {
+        const cx<T>* src = in + v * 24 * g.vh + slot_entry(g, t);
+#pragma unroll
+        for (int c = 0; c < 12; c++) buf[t * 13 + c] = src[(size_t)c * g.vh];
+    }
+    ss[t] = site_slot(g, t);
+    __syncthreads();
+    cx<double>* dst = reinterpret_cast<cx<double>*>(canon) + v * 24 * g.vh;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = t + k * LC_SITES, q = e / 12, c = e - 12 * q;
+        const SiteSlot s = ss[q];
+        if (s.canon >= 0) dst[(size_t)s.canon * 12 + c] = ccast<double>(buf[s.slot * 13 + c]);
+    }
+}
+
+template <class T>
+static void import_launch(const Geom& g, int n, const double* canon, cx<T>* out, hipStream_t s) {
+    k_import_vectors<T><<<dim3(nblk_of(2L * g.vh, LC_SITES), n), LC_SITES, 0, s>>>(g, n, canon, out);
+}
+template <class T>
+static void export_launch(const Geom& g, int n, const cx<T>* in, double* canon, hipStream_t s) {
+    k_export_vectors<T><<<dim3(nblk_of(2L * g.vh, LC_SITES), n), LC_SITES, 0, s>>>(g, n, in, canon);
 }
 
 template <class T>
@@ -73,23 +142,19 @@ void fine_import_gauge(const Geom& g, const double* canon, cx<T>* U, hipStream_t
 }
 template <class T>
 void fine_import_spinor(const Geom& g, const double* canon, cx<T>* out, hipStream_t s) {
-    long vol = 2L * g.vh;
-    k_import_vectors<T><<<nblk_of(vol, 256), 256, 0, s>>>(g, 1, canon, out);
+    import_launch(g, 1, canon, out, s);
 }
 template <class T>
 void fine_export_spinor(const Geom& g, const cx<T>* in, double* canon, hipStream_t s) {
-    long vol = 2L * g.vh;
-    k_export_vectors<T><<<nblk_of(vol, 256), 256, 0, s>>>(g, 1, in, canon);
+    export_launch(g, 1, in, canon, s);
 }
 template <class T>
 void fine_import_vectors(const Geom& g, int n, const double* canon, cx<T>* out, hipStream_t s) {
-    long vol = 2L * g.vh;
-    k_import_vectors<T><<<nblk_of(vol, 256), 256, 0, s>>>(g, n, canon, out);
+    import_launch(g, n, canon, out, s);
 }
 template <class T>
 void fine_export_vectors(const Geom& g, int n, const cx<T>* in, double* canon, hipStream_t s) {
-    long vol = 2L * g.vh;
-    k_export_vectors<T><<<nblk_of(vol, 256), 256, 0, s>>>(g, n, in, canon);
+    export_launch(g, n, in, canon, s);
 }
 
 // ---------------------------------------------------------------------------
