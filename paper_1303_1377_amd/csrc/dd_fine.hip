@@ -1829,6 +1829,14 @@ void fine_gram_schmidt(const AggMap& m, int N, const cx<T>* tv, cx<T>* P, int* b
 // D_c = P^H D P: workgroup (coarse site c, column b = hb*N + kb); slot 0
 // collects the self coupling and the hops that stay inside the aggregate's
 // lattice block, slot 1+k the hops k that leave it.  Accumulated in FP64.
+//
+// Bound by the projections onto the 2N columns (a wave sum each).  Only a face of
+// the aggregate contributes to a hop slot, so the eight slots are dealt to the
+// waves, which gather their face's sites on 64 lanes: for 4^4 aggregates one slot
+// is one wave's work, and a column costs three rounds of projections (the self
+// slot by all waves, two hop slots per wave) where running all nine slots over
+// all sites took nine.  16^4, N = 20, FP64: 11.4 -> 3.6 ms; the whole build of a level, 8x4^3
+// aggregates (two faces of 128 sites), 32.0 -> 12.8 ms; 48x24^3, 3^4, FP32 416 -> 139 ms.
 // ---------------------------------------------------------------------------
 // NT: the largest workgroup (one thread per aggregate site) the build allows;
 // the 256-thread form has the register file to keep its state without scratch
@@ -1836,7 +1844,6 @@ template <class T, int NT>
 __global__ void __launch_bounds__(NT) k_assemble_fine(FineOp<T> op, AggMap m, int N, const cx<T>* __restrict__ P,
                                                       cx<T>* __restrict__ M) {
     extern __shared__ char smem_raw[];
-    cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);  // [nw][2N]
     // workgroup (coarse site gc, column bcol); the 2N workgroups of one coarse
     // site run back to back on one XCD, sharing its L2 for the aggregate's P
     const int nd = 2 * N;
@@ -1846,75 +1853,20 @@ __global__ void __launch_bounds__(NT) k_assemble_fine(FineOp<T> op, AggMap m, in
     const int pc = gc >= m.c.vh, ic = gc - pc * m.c.vh;
     int xc[4];
     cb_coords(m.c, pc, ic, xc);
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = (blockDim.x + 63) >> 6;
-    const bool act = t < m.asz;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), nw = (blockDim.x + 63) >> 6;
+    cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);  // [nw][2N] self slot by wave
+    cx<double>* hop = red + nw * nd;                             // [8][2N] hop slots
     const int vh = m.f.vh;
-    int x[4] = {0, 0, 0, 0}, p = 0, i = 0;
-    if (act) {
-        agg_site(m, xc, t, x);
-        p = site_parity(x);
-        i = cb_index(m.f, x);
-    }
     const cx<T>* Pb = P + (size_t)kb * 24 * vh;
-    for (int slot = 0; slot < 9; slot++) {
-        cx<T> wv[12];
+    auto column = [&](int p, int i, cx<T> (&v)[12]) {   // column b of P at a site
+        load_spinor(Pb, vh, p, i, v);
 #pragma unroll
-        for (int c = 0; c < 12; c++) wv[c] = czero<T>();
-        if (act) {
-            if (slot == 0) {
-                cx<T> v[12];
-                load_spinor(Pb, vh, p, i, v);
-#pragma unroll
-                for (int c = 0; c < 12; c++)
-                    if ((c / 6) != hb) v[c] = czero<T>();
-                clover_apply(op.clov, vh, p, i, v, wv);
-                cx<T> acc[12];
-#pragma unroll
-                for (int c = 0; c < 12; c++) acc[c] = czero<T>();
-                for (int k = 0; k < 8; k++) {
-                    int y[4], yc[4];
-                    nb_coords(op.g, x, k, y);
-                    coarse_of(m, y, yc);
-                    if (yc[0] != xc[0] || yc[1] != xc[1] || yc[2] != xc[2] || yc[3] != xc[3]) continue;
-                    int j = cb_index(op.g, y);
-                    // opaque per iteration: keeps the compiler from hoisting the
-                    // neighbour's addresses out of the slot loop (they would not
-                    // fit in registers)
-                    asm volatile("" : "+v"(j));
-                    load_spinor(Pb, vh, 1 - p, j, v);
-#pragma unroll
-                    for (int c = 0; c < 12; c++)
-                        if ((c / 6) != hb) v[c] = czero<T>();
-                    hop_accum(op, k, p, i, j, v, acc);
-                }
-#pragma unroll
-                for (int c = 0; c < 12; c++) wv[c] -= T(0.5) * acc[c];
-            } else {
-                int k = slot - 1;
-                int y[4], yc[4];
-                nb_coords(op.g, x, k, y);
-                coarse_of(m, y, yc);
-                if (yc[0] != xc[0] || yc[1] != xc[1] || yc[2] != xc[2] || yc[3] != xc[3]) {
-                    int j = cb_index(op.g, y);
-                    // opaque per iteration: keeps the compiler from hoisting the
-                    // neighbour's addresses out of the slot loop (they would not
-                    // fit in registers)
-                    asm volatile("" : "+v"(j));
-                    cx<T> v[12], acc[12];
-                    load_spinor(Pb, vh, 1 - p, j, v);
-#pragma unroll
-                    for (int c = 0; c < 12; c++) {
-                        if ((c / 6) != hb) v[c] = czero<T>();
-                        acc[c] = czero<T>();
-                    }
-                    hop_accum(op, k, p, i, j, v, acc);
-#pragma unroll
-                    for (int c = 0; c < 12; c++) wv[c] = T(-0.5) * acc[c];
-                }
-            }
-        }
-        // projections onto the aggregate's columns a, AB at a time so that
-        // their loads and reductions overlap
+        for (int c = 0; c < 12; c++)
+            if ((c / 6) != hb) v[c] = czero<T>();
+    };
+    // dst[a] (+)= sum over the wave of P_a(site)^H wv, AB columns at a time so that
+    // their loads and reductions overlap
+    auto project = [&](bool act, int p, int i, const cx<T> (&wv)[12], cx<double>* dst, bool add) {
         constexpr int AB = 4;
         for (int a0 = 0; a0 < nd; a0 += AB) {
             cx<T> pa[AB][6];
@@ -1931,33 +1883,107 @@ __global__ void __launch_bounds__(NT) k_assemble_fine(FineOp<T> op, AggMap m, in
                 const int ha = ((a0 + u) / N) & 1;
                 d[u] = czero<double>();
 #pragma unroll
-                for (int c = 0; c < 6; c++) d[u] += cmulc(ccast<double>(pa[u][c]), ccast<double>(wv[6 * ha + c]));
+                for (int c = 0; c < 6; c++) d[u] += cmulc(ccast<double>(pa[u][c]), ccast<double>(ha ? wv[6 + c] : wv[c]));
             }
 #pragma unroll
             for (int u = 0; u < AB; u++) {
                 d[u].re = wave_sum(d[u].re);
                 d[u].im = wave_sum(d[u].im);
             }
-            if (lane == 0) {
+            if (lane == 0)
 #pragma unroll
                 for (int u = 0; u < AB; u++)
-                    if (a0 + u < nd) red[w * nd + a0 + u] = d[u];
+                    if (a0 + u < nd) dst[a0 + u] = add ? dst[a0 + u] + d[u] : d[u];
+        }
+    };
+    {   // self slot: one thread per site of the aggregate
+        const bool act = t < m.asz;
+        int p = 0, i = 0;
+        cx<T> wv[12];
+#pragma unroll
+        for (int c = 0; c < 12; c++) wv[c] = czero<T>();
+        if (act) {
+            int x[4];
+            agg_site(m, xc, t, x);
+            p = site_parity(x);
+            i = cb_index(m.f, x);
+            cx<T> v[12], acc[12];
+            column(p, i, v);
+            clover_apply(op.clov, vh, p, i, v, wv);
+#pragma unroll
+            for (int c = 0; c < 12; c++) acc[c] = czero<T>();
+#pragma unroll 1
+            for (int k = 0; k < 8; k++) {
+                int y[4], yc[4];
+                nb_coords(op.g, x, k, y);
+                coarse_of(m, y, yc);
+                if (yc[0] != xc[0] || yc[1] != xc[1] || yc[2] != xc[2] || yc[3] != xc[3]) continue;
+                const int j = cb_index(op.g, y);
+                column(1 - p, j, v);
+                hop_accum(op, k, p, i, j, v, acc);
             }
+#pragma unroll
+            for (int c = 0; c < 12; c++) wv[c] -= T(0.5) * acc[c];
         }
-        __syncthreads();
-        for (int a = t; a < nd; a += blockDim.x) {
-            cx<double> s = czero<double>();
+        project(act, p, i, wv, red + w * nd, false);
+    }
+#pragma unroll 1
+    for (int k = w; k < 8; k += nw) {   // hop slots: 64 sites of the face at a time
+        const int mu = k & 3;
+        // (one aggregate across the lattice: its hops are in the self slot)
+        const int face = m.c.d[mu] == 1 ? 0 : m.asz / m.a[mu];
+        if (!face)
+            for (int a = lane; a < nd; a += 64) hop[k * nd + a] = czero<double>();
+#pragma unroll 1
+        for (int f0 = 0; f0 < face; f0 += 64) {
+            const bool act = f0 + lane < face;
+            int p = 0, i = 0;
+            cx<T> wv[12];
+#pragma unroll
+            for (int c = 0; c < 12; c++) wv[c] = czero<T>();
+            if (act) {
+                int x[4], f = f0 + lane;
+#pragma unroll
+                for (int nu = 3; nu >= 0; nu--) {
+                    int l;
+                    if (nu == mu) {
+                        l = k < 4 ? m.a[nu] - 1 : 0;
+                    } else {
+                        l = f % m.a[nu];
+                        f /= m.a[nu];
+                    }
+                    x[nu] = xc[nu] * m.a[nu] + l;
+                }
+                p = site_parity(x);
+                i = cb_index(m.f, x);
+                const int j = nb_index_sel(op.g, x, k);
+                cx<T> v[12], acc[12];
+                column(1 - p, j, v);
+#pragma unroll
+                for (int c = 0; c < 12; c++) acc[c] = czero<T>();
+                hop_accum(op, k, p, i, j, v, acc);
+#pragma unroll
+                for (int c = 0; c < 12; c++) wv[c] = T(-0.5) * acc[c];
+            }
+            project(act, p, i, wv, hop + k * nd, f0 > 0);
+        }
+    }
+    __syncthreads();
+    cx<T>* out = M + ((size_t)gc * 9 * nd + bcol) * nd;   // column-major blocks
+    for (int e = t; e < 9 * nd; e += blockDim.x) {
+        const int slot = e / nd, a = e - slot * nd;
+        cx<double> s = czero<double>();
+        if (slot) s = hop[(slot - 1) * nd + a];
+        else
             for (int ww = 0; ww < nw; ww++) s += red[ww * nd + a];
-            M[(((size_t)gc * 9 + slot) * nd + bcol) * nd + a] = ccast<T>(s);  // column-major block
-        }
-        __syncthreads();
+        out[(size_t)slot * nd * nd + a] = ccast<T>(s);
     }
 }
 
 template <class T>
 void fine_assemble(const FineOp<T>& op, const AggMap& m, int N, const cx<T>* P, cx<T>* M, hipStream_t s) {
     int nt = ((m.asz + 63) / 64) * 64;
-    size_t lds = sizeof(cx<double>) * 2 * N * (nt / 64);
+    size_t lds = sizeof(cx<double>) * 2 * N * (nt / 64 + 8);
     const int nwg = 2 * m.c.vh * 2 * N;
     if (nt <= 256) k_assemble_fine<T, 256><<<nwg, nt, lds, s>>>(op, m, N, P, M);
     else k_assemble_fine<T, 1024><<<nwg, nt, lds, s>>>(op, m, N, P, M);
