@@ -329,6 +329,38 @@ __device__ __forceinline__ T wave_sum(T v) {
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// Sums over the 64 lanes of M values at once (M a multiple of 4): lane swaps
+// between the halves and between the rows of 16 put different values on them, so
+// only M/4 sums are left to take within the rows.  In row r, every lane:
+// v[j], j < M/4, holds the sum of value r * M/4 + j.  All 64 lanes must be active.
+__device__ __forceinline__ void swap_add32(double& a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void swap_add16(double& a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+template <int M>
+__device__ __forceinline__ void wave_sums(double (&v)[M]) {
+    static_assert(M % 4 == 0, "one value per row of 16 lanes");
+#pragma unroll
+    for (int j = 0; j < M / 2; j++) swap_add32(v[j], v[j + M / 2]);
+#pragma unroll
+    for (int j = 0; j < M / 4; j++) swap_add16(v[j], v[j + M / 4]);
+#pragma unroll
+    for (int j = 0; j < M / 4; j++) {
+        v[j] += dpp_move<0xB1>(v[j]);
+        v[j] += dpp_move<0x4E>(v[j]);
+        v[j] += dpp_move<0x141>(v[j]);
+        v[j] += dpp_move<0x140>(v[j]);
+    }
+}
+
 // Sum of v over the workgroup, returned to every thread.  `scratch` must hold
 // at least blockDim.x/64 values; the call synchronises the workgroup twice.
 template <class T>

@@ -1439,17 +1439,17 @@ __global__ void __launch_bounds__(NT) k_restrict_fine(AggMap m, int N, const cx<
 #pragma unroll
                 for (int c = 0; c < 12; c++) q[u][c] = czero<T>();
         }
+        double d[8] = {};   // [u][half][re, im]
 #pragma unroll
-        for (int u = 0; u < 2; u++) {
-            cx<double> d0 = czero<double>(), d1 = czero<double>();
+        for (int u = 0; u < 2; u++)
 #pragma unroll
-            for (int c = 0; c < 6; c++) d0 += ccast<double>(cmulc(q[u][c], v[c]));
-#pragma unroll
-            for (int c = 6; c < 12; c++) d1 += ccast<double>(cmulc(q[u][c], v[c]));
-            d0.re = wave_sum(d0.re); d0.im = wave_sum(d0.im);
-            d1.re = wave_sum(d1.re); d1.im = wave_sum(d1.im);
-            if (lane == 0 && (u == 0 || two)) { red[w * 2 * N + k + u] = d0; red[w * 2 * N + N + k + u] = d1; }
-        }
+            for (int c = 0; c < 12; c++) {
+                const cx<double> pr = ccast<double>(cmulc(q[u][c], v[c]));
+                d[4 * u + 2 * (c / 6)] += pr.re;
+                d[4 * u + 2 * (c / 6) + 1] += pr.im;
+            }
+        wave_sums(d);   // row of 16 lanes: u, half
+        if ((lane & 15) == 0 && (lane < 32 || two)) red[w * 2 * N + ((lane >> 4) & 1) * N + k + (lane >> 5)] = cx<double>{d[0], d[1]};
     }
     __syncthreads();
     const int kn = max(0, k1 - k0);
@@ -1493,7 +1493,10 @@ __global__ void k_prolong_fine(AggMap m, int N, const cx<S>* __restrict__ P, con
 // Restriction and prolongation for a group of KR right-hand sides: every
 // entry of P loaded from memory serves the whole group (P, N fine vectors, is
 // the bulk of the traffic).  Per RHS the sums are formed in the same order as
-// in the one-RHS kernels above.  Members of the group past the batch read the
+// in the one-RHS kernels above.  The wave sums of all members are taken together
+// and the next test vector is in flight meanwhile; a sum at a time cost more
+// than the loads (64x32^3, N = 20, FP32, four RHS: restriction 1330 -> 1068 us,
+// 4.7 TB/s).  Members of the group past the batch read the
 // first member's data and are never stored.
 template <class T, class S, int NT, int KR, class VI>
 __global__ void __launch_bounds__(NT) k_restrict_fine_k(AggMap m, int N, const cx<S>* __restrict__ P, VI in,
@@ -1535,23 +1538,35 @@ __global__ void __launch_bounds__(NT) k_restrict_fine_k(AggMap m, int N, const c
     const int kper = (N + gridDim.z - 1) / gridDim.z;
     const int k0 = blockIdx.z * kper, k1 = min(N, k0 + kper);
     const int W = KR * 2 * N;   // reduction slots per wave
-    for (int k = k0; k < k1; k++) {
-        cx<T> q[12];
-        if (act) load_spinor(P + (size_t)k * 24 * vh, vh, p, i, q);
+    auto row = [&](int k, cx<T> (&q)[12]) {
+        if (act) load_spinor(P + (size_t)min(k, k1 - 1) * 24 * vh, vh, p, i, q);
         else
 #pragma unroll
             for (int c = 0; c < 12; c++) q[c] = czero<T>();
+    };
+    cx<T> qn[12];   // the next test vector, in flight during the sums of this one
+    if (k0 < k1) row(k0, qn);
+    for (int k = k0; k < k1; k++) {
+        cx<T> q[12];
 #pragma unroll
-        for (int r = 0; r < KR; r++) {
-            cx<double> d0 = czero<double>(), d1 = czero<double>();
+        for (int c = 0; c < 12; c++) q[c] = qn[c];
+        row(k + 1, qn);
+        double d[4 * KR] = {};   // [r][half][re, im]
 #pragma unroll
-            for (int c = 0; c < 6; c++) d0 += ccast<double>(cmulc(q[c], v[r][c]));
+        for (int r = 0; r < KR; r++)
 #pragma unroll
-            for (int c = 6; c < 12; c++) d1 += ccast<double>(cmulc(q[c], v[r][c]));
-            d0.re = wave_sum(d0.re); d0.im = wave_sum(d0.im);
-            d1.re = wave_sum(d1.re); d1.im = wave_sum(d1.im);
-            if (lane == 0) { red[w * W + r * 2 * N + k] = d0; red[w * W + r * 2 * N + N + k] = d1; }
-        }
+            for (int c = 0; c < 12; c++) {
+                const cx<double> pr = ccast<double>(cmulc(q[c], v[r][c]));
+                d[4 * r + 2 * (c / 6)] += pr.re;
+                d[4 * r + 2 * (c / 6) + 1] += pr.im;
+            }
+        wave_sums(d);   // KR / 2 pairs (r, half) per row of 16 lanes
+        if ((lane & 15) == 0)
+#pragma unroll
+            for (int j = 0; j < KR / 2; j++) {
+                const int rh = (lane >> 4) * (KR / 2) + j;
+                red[w * W + rh * N + k] = cx<double>{d[2 * j], d[2 * j + 1]};
+            }
     }
     __syncthreads();
     const int kn = max(0, k1 - k0);
