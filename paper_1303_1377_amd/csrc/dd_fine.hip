@@ -1179,8 +1179,8 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
     if (!mk.on(rhs)) continue;
     const typename vrestrict<VP>::type b = b0 + rhs * ld;
     const typename vrestrict<VP>::type z = z0 + rhs * ld;
-    // half h of: e_o, rho (the odd MR residual), w, R
-    cx<T> eo[6], rho[6], w[6], R[6];
+    // half h of: e_o, rho (the odd MR residual), w, R, the even right-hand side
+    cx<T> eo[6], rho[6], w[6], R[6], be[6];
     // ---- residual on the block, b - H z ----
     // b and the hops that leave the block, in the block fields, direction by
     // direction: a site on several faces is added to by one lane at a time.  The
@@ -1230,14 +1230,15 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
     }
     __syncthreads();
     if (act) {
-        // z_e + t0 = A_e^{-1} (b - H z)_e: stored now, the rest of e_e after the MR
-        // steps, and the inner hops of r_o - D_oe t0 run over it
+        // be = (b - H z)_e with the hops only: the block's even unknowns are
+        // A_e^{-1} (be - H e_o), for e_o = 0 z_e + t0, and the inner hops of
+        // r_o - D_oe t0 run over that.  be is held until e_o is known, so that z_e
+        // is rounded (and stored in FP16) once.
         pair_hops(0, O, R);
-        lds_load6(E, bvh, h, l, w);
+        lds_load6(E, bvh, h, l, be);
 #pragma unroll
-        for (int c = 0; c < 6; c++) w[c] += T(0.5) * R[c];
-        herm6_apply(me, w, eo);
-        half_store(z, g.vh, 0, h, i, eo);
+        for (int c = 0; c < 6; c++) be[c] += T(0.5) * R[c];
+        herm6_apply(me, be, eo);
         lds_store6(E, bvh, h, l, eo);
         lds_load6(O, bvh, h, l, eo);
         herm6_apply(mo, eo, w);
@@ -1307,17 +1308,14 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
         if (act) lds_store6(O, bvh, h, l, eo);
         __syncthreads();
     }
-    // ---- back-substitution and update: z_e + t0 is in z already ----
+    // ---- back-substitution and update ----
     if (act) {
         pair_hops(0, O, R);
 #pragma unroll
-        for (int c = 0; c < 6; c++) R[c] = T(0.5) * R[c];
-        herm6_apply(me, R, w);
+        for (int c = 0; c < 6; c++) be[c] += T(0.5) * R[c];
+        herm6_apply(me, be, w);
+        half_store(z, g.vh, 0, h, i, w);
         cx<T> zh[6];
-        half_load(z, g.vh, 0, h, i, zh);
-#pragma unroll
-        for (int c = 0; c < 6; c++) zh[c] += w[c];
-        half_store(z, g.vh, 0, h, i, zh);
         half_load(z, g.vh, 1, h, i, zh);
 #pragma unroll
         for (int c = 0; c < 6; c++) zh[c] += eo[c];
