@@ -49,7 +49,8 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
         gm_fold(isc, blockIdx.y);
         return;
     }
-    if (!mk.on(blockIdx.y)) return;
+    __shared__ int run;
+    if (!wg_enter(mk, isc, blockIdx.y, run)) return;
     {
         const long off = blockIdx.y * ld;
         if (in1) in1 += off;
@@ -109,6 +110,7 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
         if (isc.which & 2) f2 *= f;
     }
     __syncthreads();
+    if (isc.npart && !run) return;
     for (int e = threadIdx.x; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
         X[e] = ((s2 >= nself) ? f2 : f1) * vin[s2][e - s2 * nd];
@@ -303,7 +305,9 @@ __global__ void __launch_bounds__((MfmaWg<S, NS, MG>::NT)) k_coarse_apply_mfma(C
     const int r = 16 * w + j;
     const int nself = (self_mode == CS_SELF || self_mode == CS_SELFINV) ? 1 : 0;
     const int ns = nself + (hop_sign != 0 ? 8 : 0);
-    // lane k holds flag and factor of right-hand side k: one load for all
+    // lane k holds flag and factor of right-hand side k: one load for all (beside a
+    // fold the waves may see a flag before and after it is raised: such a column is
+    // staged and stored in part, and nothing reads it)
     const bool mine = lane < nr && mk.on(lane);
     double f0 = (isc.st && !isc.npart && lane < nr) ? isc.st[lane].sc[isc.j] : 1.0;
     const unsigned on = (unsigned)__ballot(mine);
@@ -590,7 +594,8 @@ __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par,
     }
     constexpr int CG = 64 / RC;          // column groups per wavefront
     constexpr int PF = (CG >= 4) ? 12 * (8 / CG) : 24;   // block entries a lane loads at once
-    if (!mk.on(blockIdx.y)) return;
+    __shared__ int run;
+    if (!wg_enter(mk, isc, blockIdx.y, run)) return;
     {
         const long off = blockIdx.y * ld;
         if (in1) in1 += off;
@@ -644,6 +649,7 @@ __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par,
     }
     if (hop_sign < 0) f2 = -f2;
     __syncthreads();
+    if (isc.npart && !run) return;
     for (int e = t; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
         const cx<T> v = vin[s2][e - s2 * nd];

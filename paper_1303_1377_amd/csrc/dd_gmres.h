@@ -8,8 +8,9 @@
 // meanwhile: neither waits for the other, and the update kernel needs no last
 // workgroup that runs the rotations while the device is idle (16^4, FP64:
 // update 13.0 us with them, 4.7 us without; 6x3^3, FP32, four right-hand
-// sides: 18.7 -> 5.5 us).  A stop found there is seen from
-// the next kernel on; what the first kernel writes is scratch.
+// sides: 18.7 -> 5.5 us).  A stop found there may be seen by some workgroups of
+// that launch and is seen by every kernel after it; what the first kernel writes
+// for such a right-hand side is scratch.
 #pragma once
 #include "dd_kernels.h"
 
@@ -76,6 +77,17 @@ __device__ __forceinline__ void gm_column_wg(GmDev* st, int j, const cx<double>*
         st->sc[j + 1] = st->scale;   // the new basis vector keeps its factor
         st->stop = stop;
     }
+}
+
+// Whether the workgroup works on right-hand side r.  Beside a fold (isc.npart) the
+// flag may be raised while the launch runs and the waves would read it before and
+// after: one thread then reads it for all, and the workgroup takes the decision
+// from `run` behind its first barrier.  (Waves that went on without the others
+// would read input pointers in LDS that nobody had stored.)
+__device__ __forceinline__ bool wg_enter(const Mask& mk, const InScale& isc, int r, int& run) {
+    if (!isc.npart) return mk.on(r);
+    if (threadIdx.x == 0) run = mk.on(r);
+    return true;
 }
 
 // The extra workgroup of the first kernel of a step: column isc.j - 1 of
