@@ -795,12 +795,12 @@ void fine_dirac_from32(const FineOp<double>& op, const cx<float>* in, cx<double>
 // The residual b - H z splits its hops.  Those inside the block run like the MR
 // steps' over z staged in the block fields.  Those that leave it (a quarter of
 // all hops for 4^4 blocks) are dealt evenly to the lanes, one (side, face site,
-// spin) each per direction, and added to b in the block fields first.  Walking the
+// spin) each per direction, and summed in the block fields first.  Walking the
 // eight hops of a site with every lane gathering cost one memory round trip per
 // hop at two waves per SIMD (1285 of 1985 us), and -H_int t0 another sum.  Half
-// sweep, 64x32^3, FP32, 4 RHS: 863 us + 187 us per MR step, the latter at the
-// issue rate of the vector unit; with 4 MR steps 1985 -> 1608 us.  16^4, 3 MR
-// steps: FP64 57.4 -> 54.1 us, FP32 52.5 -> 42.4 us.
+// sweep, 64x32^3, FP32, 4 RHS: 855 us + 181 us per MR step, the latter at the
+// issue rate of the vector unit; with 4 MR steps 1985 -> 1579 us.  16^4, 3 MR
+// steps: FP64 57.4 -> 53.4 us, FP32 52.5 -> 42.8 us.
 // ---------------------------------------------------------------------------
 struct LinkMap {        // compact index of the block-internal links of direction mu
     int ext[4][4];      // box extents per direction
@@ -844,12 +844,6 @@ __device__ __forceinline__ void su3_rebuild(cx<T> u[9]) {
     u[6] = cross(u[1], u[5], u[2], u[4]);
     u[7] = cross(u[2], u[3], u[0], u[5]);
     u[8] = cross(u[0], u[4], u[1], u[3]);
-}
-
-template <class T>
-__device__ __forceinline__ void lds_store(cx<T>* buf, int bvh, int l, const cx<T> v[12]) {
-#pragma unroll
-    for (int c = 0; c < 12; c++) buf[c * bvh + l] = v[c];
 }
 
 // Hops that leave the block in direction MU, over its two faces: 2 n of them for
@@ -1097,8 +1091,8 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
     // both sites' block vectors and of both clover blocks, so every clover
     // product and MR update is local to the lane; a hopping sum is split over
     // the pair by direction (lane h: mu = 2h, 2h + 1) and the halves meet
-    // through one lane swap.  Only the residual, with its hops to other blocks,
-    // is computed per site (lane h: the site of parity h).
+    // through one lane swap.  Only the residual's hops to other blocks are dealt to
+    // the lanes by the faces of the block.
     const int t = threadIdx.x;
     const bool act = t < 2 * bvh;
     const int h = t & 1;
@@ -1182,9 +1176,12 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
     // half h of: e_o, rho (the odd MR residual), w, R, the even right-hand side
     cx<T> eo[6], rho[6], w[6], R[6], be[6];
     // ---- residual on the block, b - H z ----
-    // b and the hops that leave the block, in the block fields, direction by
+    // The hops that leave the block, summed in the block fields direction by
     // direction: a site on several faces is added to by one lane at a time.  The
-    // next direction's gathers are in flight while one is added.
+    // next direction's gathers are in flight while one is added.  b joins the whole
+    // sum: added to b one by one, each hop rounded at the size of b (FP32, error of a
+    // sweep against FP64: 1.36e-7 so, 1.29e-7 now with 2^4 blocks, 1.35e-7 and 1.32e-7
+    // with 4^4).
     {
         // opaque per right-hand side: keeps the compiler from hoisting the links and
         // all their addresses out of the loop (they would not fit in registers)
@@ -1193,9 +1190,9 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
         FaceData<T> da, db;
         face_load<0>(op, f0, base, z, da);
         if (act) {
-            cx<T> v[12];
-            load_spinor(b, g.vh, h, i, v);
-            lds_store(h ? O : E, bvh, l, v);
+            cx<T>* fld = h ? O : E;
+#pragma unroll
+            for (int c = 0; c < 12; c++) fld[c * bvh + l] = czero<T>();
         }
         face_load<1>(op, f1, base, z, db);
         __syncthreads();
@@ -1206,6 +1203,10 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
         face_load<3>(op, f3, base, z, db);
         __syncthreads();
         face_add<2>(f2, bvh, E, O, da);
+        if (act) {
+            half_load(b, g.vh, 0, h, i, be);
+            half_load(b, g.vh, 1, h, i, rho);
+        }
         __syncthreads();
         face_add<3>(f3, bvh, E, O, db);
         __syncthreads();
@@ -1225,7 +1226,9 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
     if (act) {
         cx<T> zh[6];
         half_load(z, g.vh, 1, h, i, zh);
-        lds_load6(O, bvh, h, l, rho);
+        lds_load6(O, bvh, h, l, w);
+#pragma unroll
+        for (int c = 0; c < 6; c++) rho[c] += w[c];
         lds_store6(O, bvh, h, l, zh);   // each lane overwrites only the half it read
     }
     __syncthreads();
@@ -1235,9 +1238,9 @@ __global__ void __launch_bounds__(256, MINW) k_sap_fine(FineOp<T, S> op, const i
         // r_o - D_oe t0 run over that.  be is held until e_o is known, so that z_e
         // is rounded (and stored in FP16) once.
         pair_hops(0, O, R);
-        lds_load6(E, bvh, h, l, be);
+        lds_load6(E, bvh, h, l, w);
 #pragma unroll
-        for (int c = 0; c < 6; c++) be[c] += T(0.5) * R[c];
+        for (int c = 0; c < 6; c++) be[c] += w[c] + T(0.5) * R[c];
         herm6_apply(me, be, eo);
         lds_store6(E, bvh, h, l, eo);
         lds_load6(O, bvh, h, l, eo);
