@@ -40,17 +40,22 @@ template <class S> struct CaPre {
     static constexpr int INV = sizeof(S) > 4 ? 4 : 8;
 };
 
-template <class T, class S>
+// FOLD: the first kernel of an Arnoldi step, which also folds the step before
+// (compiled apart: the fold's registers cost the FP16-storage row kernel a wave
+// per SIMD, 80 -> 90 registers, 8^4 sites of 32 unknowns 36 -> 41 us)
+template <class T, class S, bool FOLD = true>
 __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> op, int par, int self_mode,
                                                                 const cx<T>* __restrict__ in1, int hop_sign,
                                                                 const cx<T>* in2, int post_inv, cx<T>* out,
                                                                 Mask mk, long ld, InScale isc, int nsite) {
-    if ((int)blockIdx.x >= nsite) {   // the extra workgroup of a first Arnoldi kernel
-        gm_fold(isc, blockIdx.y);
-        return;
-    }
     __shared__ int run;
-    if (!wg_enter(mk, isc, blockIdx.y, run)) return;
+    if constexpr (FOLD) {
+        if ((int)blockIdx.x >= nsite) {   // the extra workgroup
+            gm_fold(isc, blockIdx.y);
+            return;
+        }
+    }
+    if (!wg_enter<FOLD>(mk, blockIdx.y, run)) return;
     {
         const long off = blockIdx.y * ld;
         if (in1) in1 += off;
@@ -105,12 +110,12 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
     if (post_inv) load_inv(c0);
     T f1 = T(1), f2 = T(hop_sign < 0 ? -1 : 1);
     if (isc.st) {
-        const T f = T(gm_factor(isc, blockIdx.y));
+        const T f = T(FOLD ? gm_factor(isc, blockIdx.y) : isc.st[blockIdx.y].sc[isc.j]);
         if (isc.which & 1) f1 *= f;
         if (isc.which & 2) f2 *= f;
     }
     __syncthreads();
-    if (isc.npart && !run) return;
+    if (FOLD && !run) return;
     for (int e = threadIdx.x; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
         X[e] = ((s2 >= nself) ? f2 : f1) * vin[s2][e - s2 * nd];
@@ -583,19 +588,21 @@ static void mfma_launch(const CoarseOp<float, S>& op, int nsite, int par, int se
 // groups meet through lane shuffles and the wavefronts in LDS.  No post
 // multiplication: the folded blocks carry the self inverse where it is needed.
 // ---------------------------------------------------------------------------
-template <class T, class S, int RC>
+template <class T, class S, int RC, bool FOLD = true>
 __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par, int self_mode,
                                                      const cx<T>* __restrict__ in1, int hop_sign, int fold,
                                                      const cx<T>* in2, cx<T>* out, Mask mk, long ld, InScale isc,
                                                      int nwg) {
-    if ((int)blockIdx.x >= nwg) {   // the extra workgroup of a first Arnoldi kernel
-        gm_fold(isc, blockIdx.y);
-        return;
-    }
     constexpr int CG = 64 / RC;          // column groups per wavefront
     constexpr int PF = (CG >= 4) ? 12 * (8 / CG) : 24;   // block entries a lane loads at once
     __shared__ int run;
-    if (!wg_enter(mk, isc, blockIdx.y, run)) return;
+    if constexpr (FOLD) {
+        if ((int)blockIdx.x >= nwg) {   // the extra workgroup
+            gm_fold(isc, blockIdx.y);
+            return;
+        }
+    }
+    if (!wg_enter<FOLD>(mk, blockIdx.y, run)) return;
     {
         const long off = blockIdx.y * ld;
         if (in1) in1 += off;
@@ -643,13 +650,13 @@ __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par,
     // factors of the two inputs (stored GMRES basis vectors carry theirs in the state)
     T f1 = T(1), f2 = T(1);
     if (isc.st) {
-        const T f = T(gm_factor(isc, blockIdx.y));
+        const T f = T(FOLD ? gm_factor(isc, blockIdx.y) : isc.st[blockIdx.y].sc[isc.j]);
         if (isc.which & 1) f1 = f;
         if (isc.which & 2) f2 = f;
     }
     if (hop_sign < 0) f2 = -f2;
     __syncthreads();
-    if (isc.npart && !run) return;
+    if (FOLD && !run) return;
     for (int e = t; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
         const cx<T> v = vin[s2][e - s2 * nd];
@@ -685,9 +692,12 @@ static void launch_rows(const CoarseOp<T, S>& op, int par, int self_mode, const 
     constexpr int RC = 128 / (int)sizeof(cx<S>);   // rows per 128-byte line
     const int nsite = (par < 0) ? 2 * op.g.vh : op.g.vh;
     const int nrc = (op.nd + RC - 1) / RC;
-    dim3 grid(nsite * nrc + (isc.npart ? 1 : 0), nr);
-    k_coarse_rows<T, S, RC><<<grid, 256, 0, s>>>(op, par, self_mode, in1, hop_sign, fold, in2, out, mk, ld, isc,
-                                                 nsite * nrc);
+    auto go = [&](auto kernel) {
+        dim3 grid(nsite * nrc + (isc.npart ? 1 : 0), nr);
+        kernel<<<grid, 256, 0, s>>>(op, par, self_mode, in1, hop_sign, fold, in2, out, mk, ld, isc, nsite * nrc);
+    };
+    if (isc.npart) go(k_coarse_rows<T, S, RC, true>);
+    else go(k_coarse_rows<T, S, RC, false>);
 }
 
 // B_k(x) = Minv(x) M_{1+k}(x): workgroup (even site i, hop k), FP64 sums
@@ -751,9 +761,12 @@ void coarse_apply(const CoarseOp<T, S>& op, int par, int self_mode, const cx<T>*
     // workgroup size allows
     int nw = std::max(1, std::min(CA_WAVES, (nslot * op.nd + CaPre<S>::N - 1) / CaPre<S>::N));
     if (post_inv) nw = std::max(nw, std::min(CA_WAVES, (op.nd + CaPre<S>::INV - 1) / CaPre<S>::INV));
-    dim3 grid(nsite + (isc.npart ? 1 : 0), nr);
-    k_coarse_apply<T, S><<<grid, 64 * nw, 0, s>>>(op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, isc,
-                                                  nsite);
+    auto go = [&](auto kernel) {
+        dim3 grid(nsite + (isc.npart ? 1 : 0), nr);
+        kernel<<<grid, 64 * nw, 0, s>>>(op, par, self_mode, in1, hop_sign, in2, post_inv ? 1 : 0, out, mk, ld, isc, nsite);
+    };
+    if (isc.npart) go(k_coarse_apply<T, S, true>);
+    else go(k_coarse_apply<T, S, false>);
 }
 
 // ---------------------------------------------------------------------------

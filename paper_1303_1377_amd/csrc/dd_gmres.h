@@ -79,13 +79,14 @@ __device__ __forceinline__ void gm_column_wg(GmDev* st, int j, const cx<double>*
     }
 }
 
-// Whether the workgroup works on right-hand side r.  Beside a fold (isc.npart) the
-// flag may be raised while the launch runs and the waves would read it before and
-// after: one thread then reads it for all, and the workgroup takes the decision
-// from `run` behind its first barrier.  (Waves that went on without the others
-// would read input pointers in LDS that nobody had stored.)
-__device__ __forceinline__ bool wg_enter(const Mask& mk, const InScale& isc, int r, int& run) {
-    if (!isc.npart) return mk.on(r);
+// Whether the workgroup works on right-hand side r.  Beside a fold the flag may be
+// raised while the launch runs and the waves would read it before and after: one
+// thread then reads it for all, and the workgroup takes the decision from `run`
+// behind its first barrier.  (Waves that went on without the others would read
+// input pointers in LDS that nobody had stored.)
+template <bool FOLD>
+__device__ __forceinline__ bool wg_enter(const Mask& mk, int r, int& run) {
+    if constexpr (!FOLD) return mk.on(r);
     if (threadIdx.x == 0) run = mk.on(r);
     return true;
 }

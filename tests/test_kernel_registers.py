@@ -57,3 +57,10 @@ def test_fine_sap_stays_in_registers(kernels):
     assert len(sap) == 10
     for n, k in sap.items():
         assert k[".vgpr_spill_count"] <= 16 and k[".private_segment_fixed_size"] <= 128, n
+
+
+def test_row_kernel_without_a_fold(kernels):
+    """The row-split coarse stencil of FP16 storage keeps six waves per SIMD where it
+    folds no Arnoldi step."""
+    rows = [k for n, k in kernels.items() if "k_coarse_rowsIfDF16_" in n and "Lb1E" not in n]
+    assert rows and all(k[".vgpr_count"] <= 80 for k in rows)
