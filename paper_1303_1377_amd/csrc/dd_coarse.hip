@@ -1280,6 +1280,9 @@ static constexpr int CS_NT = 1024;
 static constexpr int CS_PARTS = 12;   // lane groups that share a site's columns, at most
 static constexpr size_t CS_LDS = 150 * 1024;   // of the CU's 160 KB
 
+// columns that a lane has in flight at once
+__host__ __device__ constexpr int coarse_sap_cols(size_t t, int rows_rhs) { return t == 8 || rows_rhs > 8 ? 3 : 4; }
+
 // rows of a block column in one load; KR vector entries at one row
 template <class S, int RPL> struct alignas(sizeof(cx<S>) * RPL) RowPack { cx<S> v[RPL]; };
 template <class T, int KR> struct alignas(sizeof(cx<T>) * KR > 16 ? 16 : sizeof(cx<T>) * KR) RhsPack { cx<T> v[KR]; };
@@ -1362,7 +1365,7 @@ __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const i
     const size_t nn = (size_t)nd * nd;
     const int LC = nd / RPL, NG = nt / LC;
     const int grp = t / LC, r0 = (t - grp * LC) * RPL;
-    constexpr int U = sizeof(T) == 8 || RPL * KR > 8 ? 3 : 4;
+    constexpr int U = coarse_sap_cols(sizeof(T), RPL * KR);
     // partial rows of a product, for the lane groups' (site, part) tasks:
     // entry e < count(l) of site l reads the block at base(l) + slot nn and the vector at offset xo
     auto product = [&](auto&& base, auto&& count, auto&& entry) {
@@ -1599,6 +1602,7 @@ __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const i
 struct SapShape {
     bool ok, big;
     int nt, nv, parts, hops;
+    long units;   // block fields that LDS has left for partial rows and staged hops
     size_t lds;
 };
 template <class T>
@@ -1608,21 +1612,35 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
     const int lc = nd / rpl, f = bv * nd * kr;
     const size_t unit = sizeof(cx<T>) * f;
     const size_t fixed = sizeof(cx<T>) * 2 * kr + sizeof(double) * 3 * kr * (CS_NT / 64) + (size_t)(big ? 48 : 112) * bv;
-    const long units = (long)((CS_LDS - fixed) / unit) - 2;
-    if (units < 2) return s;
-    // parts: the fewest rounds of the lane groups per column, with at most
-    // CS_PARTS partial rows to add and LDS left for a staged hop
+    s.units = (long)((CS_LDS - fixed) / unit) - 2;
+    if (s.units < 2) return s;
+    // Parts: a phase takes the rounds of the lane groups, each the batches of columns
+    // that a group loads one after another (a column adds a twentieth of a batch); a
+    // round of staged hops, a partial row to add and the size of the workgroup count
+    // little.  The weights are a fit to 186 timed shapes (2^4, 2x4^3, 2x3^3, 4^2x2^2,
+    // 4^4; 4 to 60 unknowns; every storage; one and eight right-hand sides; all parts):
+    // 2 % above the best parts in the mean, 22 % at most.  The fewest rounds alone
+    // were 11 % above in the mean and up to 2.1 times: LDS left for one staged hop, or
+    // batches half empty.
+    const int u = coarse_sap_cols(sizeof(T), rpl * kr);
     double best = 0;
-    for (int p = 1; p <= CS_PARTS && p < units && p <= nd; p++) {
-        const double cost = (double)((bv * p + CS_NT / lc - 1) / (CS_NT / lc)) / p;
-        if (p == 1 || cost < best - 1e-9) { best = cost; s.parts = p; }
+    for (int p = 1; p <= CS_PARTS && p < s.units && p <= nd; p++) {
+        const int work = std::max(std::min(bv * p * lc, CS_NT), (f + 2) / 3);
+        const int nt = std::min(CS_NT, (work + 63) / 64 * 64), groups = std::max(1, nt / lc);
+        // the nine slots of the residual in one round, or in two, three, five
+        const long left = s.units - p;
+        const int hops = left >= 9 ? 9 : left >= 5 ? 5 : left >= 3 ? 3 : left >= 2 ? 2 : 1;
+        const int columns = (nd + p - 1) / p;
+        const int rounds = (bv * p + groups - 1) / groups, staged = (9 + hops - 1) / hops + (8 + hops - 1) / hops;
+        const double cost = rounds * ((columns + u - 1) / u + 0.05 * columns) + 0.1 * staged +
+                            0.05 * p * ((f + nt - 1) / nt) + 0.05 * nt / 256;
+        if (p > 1 && cost >= best) continue;
+        best = cost;
+        s.parts = p;
+        s.hops = hops;
+        s.nt = nt;
     }
-    const int work = std::max(std::min(bv * s.parts * lc, CS_NT), (f + 2) / 3);
-    s.nt = std::min(CS_NT, (work + 63) / 64 * 64);
     s.nv = (f + s.nt - 1) / s.nt;
-    // the nine slots of the residual in one round, or in two, three, five
-    const long left = units - s.parts;
-    s.hops = left >= 9 ? 9 : left >= 5 ? 5 : left >= 3 ? 3 : left >= 2 ? 2 : 1;
     s.lds = unit * (2 + s.parts + s.hops) + fixed;
     s.ok = s.nv <= 3 && lc <= CS_NT;
     return s;
@@ -1661,11 +1679,11 @@ static void coarse_sap_pick(const CoarseOp<T, S>& op, const int* blocks, int nbl
     auto want = [&](int kr) { return nr > kr / 2 && nblocks * ((nr + kr - 1) / kr) >= 128; };
     if constexpr (sizeof(T) == 4 && (sizeof(S) != 2 || RPL == 4)) {
         const SapShape s4 = coarse_sap_shape<T>(bv, op.nd, 4, RPL);
-        if (s4.ok && s4.parts + s4.hops >= 6 && want(4)) return launch(std::integral_constant<int, 4>{}, s4);
+        if (s4.ok && s4.units >= 6 && want(4)) return launch(std::integral_constant<int, 4>{}, s4);
     }
     if constexpr (sizeof(S) != 2 || RPL == 4) {
         const SapShape s2 = coarse_sap_shape<T>(bv, op.nd, 2, RPL);
-        if (s2.ok && s2.parts + s2.hops >= 4 && want(2)) return launch(std::integral_constant<int, 2>{}, s2);
+        if (s2.ok && s2.units >= 6 && want(2)) return launch(std::integral_constant<int, 2>{}, s2);
     }
     const SapShape s1 = coarse_sap_shape<T>(bv, op.nd, 1, RPL);
     if (s1.ok) return launch(std::integral_constant<int, 1>{}, s1);
