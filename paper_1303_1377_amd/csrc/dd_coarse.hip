@@ -275,7 +275,13 @@ struct TileFrags {
 //   each other's waits, which beats the deeper loads once every CU has several
 //   sites: 64x32^3 level 1 (8192 sites) 284 -> 213 us (4.4 TB/s), against 360 us
 //   for MG = 3.
-// The line between them is 1024 sites, four for each CU.
+// Both forms timed for 1 to 30 test vectors N (2 N unknowns), 256 to 16384 sites
+// and 2 to 16 right-hand sides.  With two row tiles or more the line is 1024 sites:
+// FP32, N = 10..16, MG = 3 takes 0.7-0.8 of the time of MG = 1 at 512 sites, 1.0-1.2
+// at 1024; FP16 storage, N = 20, 0.72 and 1.3 (FP32, N >= 20, crosses earlier: 0.77 at
+// 256, 1.2 at 512).  With one tile (N <= 8) it is 2048: 0.8-1.0 at 1296, 0.9-1.2 at
+// 2592; and as the one wave of MG = 1 stages all nine slots, MG = 3 serves every
+// size from 128 entries per slot on (16384 sites, FP32, N = 5..8, eight RHS: 0.85).
 template <class S, int NS, int MG> struct MfmaWg {
     static constexpr int NT = 64 * MG * ((NS * MfmaK<S>::K + 15) / 16);
 };
@@ -323,8 +329,17 @@ __global__ void __launch_bounds__((MfmaWg<S, NS, MG>::NT)) k_coarse_apply_mfma(C
     constexpr int SR = 3, PS = MG == 1 ? 3 : 1;   // entries per slot and slots asked for ahead
     int x[4];
     cb_coords(g, p, i, x);
+    // MG = 1: lane k finds neighbour k; a wave that stages several slots would find
+    // them one after another (8^4 sites of 4 unknowns, FP32, two RHS: 16.4 -> 14.2 us).
+    // With MG = 3 a wave has one slot, or three (one by one is 4 % faster there: 24
+    // against 25 us at 512 sites of 36 unknowns)
+    int nb = 0;
+    if constexpr (MG == 1) nb = (int)nb_global(g, p, x, lane & 7);
     auto input = [&](int sl) {
-        return sl < nself ? in1 + gs * nd : in2 + nb_global(g, p, x, sl - nself) * nd;
+        if (sl < nself) return in1 + gs * nd;
+        const int k = sl - nself;
+        if constexpr (MG == 1) return in2 + (size_t)__builtin_amdgcn_readlane(nb, k) * nd;
+        else return in2 + nb_global(g, p, x, k) * nd;
     };
     auto entry = [&](const cx<float>* v, int e) {
         const int k = e / NDK, c = e - k * NDK;
@@ -553,10 +568,12 @@ static void mfma_launch(const CoarseOp<float, S>& op, int nsite, int par, int se
                         InScale isc) {
     auto pick = [&](auto ns) {
         constexpr int NS = decltype(ns)::value;
+        const bool one = op.nd <= 16;
+        const bool split = nsite < (one ? 2048 : 1024) || (one && NS * MfmaK<S>::K * mfma_cols(nr) >= 128);
         auto go = [&](auto pack, auto n) {
             constexpr bool P = decltype(pack)::value;
             constexpr int ND = decltype(n)::value;
-            if (nsite < 1024) mfma_go<S, NS, P, ND, 3>(op, nsite, par, self_mode, in1, hop_sign, in2, post_inv, out, s, mk, nr, ld, isc);
+            if (split) mfma_go<S, NS, P, ND, 3>(op, nsite, par, self_mode, in1, hop_sign, in2, post_inv, out, s, mk, nr, ld, isc);
             else mfma_go<S, NS, P, ND, 1>(op, nsite, par, self_mode, in1, hop_sign, in2, post_inv, out, s, mk, nr, ld, isc);
         };
         constexpr std::integral_constant<int, 0> any{};
@@ -567,13 +584,17 @@ static void mfma_launch(const CoarseOp<float, S>& op, int nsite, int par, int se
     };
     const int steps = (op.nd + MfmaK<S>::K - 1) / MfmaK<S>::K;
     if constexpr (std::is_same<S, float>::value) {
-        if (steps <= 5) pick(std::integral_constant<int, 5>{});
+        if (steps <= 1) pick(std::integral_constant<int, 1>{});
+        else if (steps <= 2) pick(std::integral_constant<int, 2>{});
+        else if (steps <= 4) pick(std::integral_constant<int, 4>{});
+        else if (steps <= 5) pick(std::integral_constant<int, 5>{});
         else if (steps <= 8) pick(std::integral_constant<int, 8>{});
         else if (steps <= 10) pick(std::integral_constant<int, 10>{});
         else if (steps <= 12) pick(std::integral_constant<int, 12>{});
         else pick(std::integral_constant<int, 16>{});
     } else {
-        if (steps <= 2) pick(std::integral_constant<int, 2>{});
+        if (steps <= 1) pick(std::integral_constant<int, 1>{});
+        else if (steps <= 2) pick(std::integral_constant<int, 2>{});
         else if (steps <= 3) pick(std::integral_constant<int, 3>{});
         else pick(std::integral_constant<int, 4>{});
     }
