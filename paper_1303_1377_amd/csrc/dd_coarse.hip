@@ -1309,7 +1309,9 @@ template <class S, int RPL> struct alignas(sizeof(cx<S>) * RPL) RowPack { cx<S> 
 template <class T, int KR> struct alignas(sizeof(cx<T>) * KR > 16 ? 16 : sizeof(cx<T>) * KR) RhsPack { cx<T> v[KR]; };
 
 // BIG: blocks of many sites with few unknowns, whose neighbour table does not
-// fit in LDS beside the fields: neighbours are found again where they are read
+// fit in LDS beside the fields: neighbours are found again where they are read, and
+// the staged hops take no fields of their own.  Three fields and 48 bytes per site
+// then hold every block of 2048 rows (1024 sites of 2 unknowns in FP64: 148 KB)
 template <class T, class S, int KR, int RPL, int NV, bool BIG>
 __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const int* __restrict__ blocks, SapTab tab, int bv,
                                                       const cx<T>* __restrict__ b, cx<T>* __restrict__ z, int mr_steps,
@@ -1330,7 +1332,8 @@ __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const i
     const int F = bv * nd * KR;                          // entries of one block field
     cx<T>* so = reinterpret_cast<cx<T>*>(smem_raw);      // odd-site field
     cx<T>* se = so + F;                                  // even-site field
-    cx<T>* sg = se + F;                                  // staged hop inputs [H][F]
+    // staged hop inputs [H][F] (BIG: H = 2, in the two fields, which are free meanwhile)
+    cx<T>* sg = BIG ? so : se + F;
     cx<T>* pr = sg + (size_t)H * F;                      // partial rows [parts][F]
     cx<T>* zero = pr + (size_t)parts * F;                // KR zeros (columns past a group's last)
     double* red = reinterpret_cast<double*>(zero + 2 * KR);   // [waves][KR][3]
@@ -1634,7 +1637,7 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
     const size_t unit = sizeof(cx<T>) * f;
     const size_t fixed = sizeof(cx<T>) * 2 * kr + sizeof(double) * 3 * kr * (CS_NT / 64) + (size_t)(big ? 48 : 112) * bv;
     s.units = (long)((CS_LDS - fixed) / unit) - 2;
-    if (s.units < 2) return s;
+    if (s.units < (big ? 1 : 2)) return s;
     // Parts: a phase takes the rounds of the lane groups, each the batches of columns
     // that a group loads one after another (a column adds a twentieth of a batch); a
     // round of staged hops, a partial row to add and the size of the workgroup count
@@ -1645,12 +1648,12 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
     // batches half empty.
     const int u = coarse_sap_cols(sizeof(T), rpl * kr);
     double best = 0;
-    for (int p = 1; p <= CS_PARTS && p < s.units && p <= nd; p++) {
+    for (int p = 1; p <= CS_PARTS && p < s.units + big && p <= nd; p++) {
         const int work = std::max(std::min(bv * p * lc, CS_NT), (f + 2) / 3);
         const int nt = std::min(CS_NT, (work + 63) / 64 * 64), groups = std::max(1, nt / lc);
         // the nine slots of the residual in one round, or in two, three, five
         const long left = s.units - p;
-        const int hops = left >= 9 ? 9 : left >= 5 ? 5 : left >= 3 ? 3 : left >= 2 ? 2 : 1;
+        const int hops = big ? 2 : left >= 9 ? 9 : left >= 5 ? 5 : left >= 3 ? 3 : left >= 2 ? 2 : 1;
         const int columns = (nd + p - 1) / p;
         const int rounds = (bv * p + groups - 1) / groups, staged = (9 + hops - 1) / hops + (8 + hops - 1) / hops;
         const double cost = rounds * ((columns + u - 1) / u + 0.05 * columns) + 0.1 * staged +
@@ -1662,7 +1665,7 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
         s.nt = nt;
     }
     s.nv = (f + s.nt - 1) / s.nt;
-    s.lds = unit * (2 + s.parts + s.hops) + fixed;
+    s.lds = unit * (2 + s.parts + (big ? 0 : s.hops)) + fixed;
     s.ok = s.nv <= 3 && lc <= CS_NT;
     return s;
 }
