@@ -368,6 +368,8 @@ __global__ void __launch_bounds__((MfmaWg<S, NS, MG>::NT)) k_coarse_apply_mfma(C
     } else if (wv == 0 && lane < nr) {
         put_factor(lane, f0);
     }
+    // columns of the tile beyond the batch: their inputs are zero, so they stay zero
+    if (wv == 0 && lane >= nr && lane < xs) put_factor(lane, 1.0);
     auto block = [&](int sl) {
         return sl < nself ? (self_mode == CS_SELF ? op.M + gs * 9 * nn : op.Minv + gs * nn) : op.M + (gs * 9 + 1 + sl - nself) * nn;
     };
@@ -1311,7 +1313,7 @@ template <class T, int KR> struct alignas(sizeof(cx<T>) * KR > 16 ? 16 : sizeof(
 // BIG: blocks of many sites with few unknowns, whose neighbour table does not
 // fit in LDS beside the fields: neighbours are found again where they are read, and
 // the staged hops take no fields of their own.  Three fields and 48 bytes per site
-// then hold every block of 2048 rows (1024 sites of 2 unknowns in FP64: 148 KB)
+// then hold every block of 2048 rows (1024 sites of 2 unknowns in FP64: 144 KB)
 template <class T, class S, int KR, int RPL, int NV, bool BIG>
 __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const int* __restrict__ blocks, SapTab tab, int bv,
                                                       const cx<T>* __restrict__ b, cx<T>* __restrict__ z, int mr_steps,
