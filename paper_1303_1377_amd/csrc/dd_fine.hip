@@ -1527,10 +1527,14 @@ __global__ void k_prolong_fine(AggMap m, int N, const cx<S>* __restrict__ P, con
 // entry of P loaded from memory serves the whole group (P, N fine vectors, is
 // the bulk of the traffic).  Per RHS the sums are formed in the same order as
 // in the one-RHS kernels above.  The wave sums of all members are taken together
-// and the next test vector is in flight meanwhile; a sum at a time cost more
-// than the loads (64x32^3, N = 20, FP32, four RHS: restriction 1330 -> 1068 us,
-// 4.7 TB/s).  Members of the group past the batch read the
-// first member's data and are never stored.
+// and the next test vector is in flight meanwhile; a sum at a time, through LDS
+// shuffles, cost more than the loads (64x32^3, N = 20, four RHS: FP32 1576 -> 849
+// us, 5.7 TB/s; FP16 storage 1573 -> 759).  The vector in flight is kept as it is
+// stored and nothing is asked for past the last one: converted as it arrived, and
+// the last read twice, it took 933 and 886 us, and with 3^4 aggregates up to a
+// tenth longer than without (24^4, N = 5, FP32, three RHS: 327, 362, now 315 us).
+// Members of the group past the batch read the first member's data and are never
+// stored.
 template <class T, class S, int NT, int KR, class VI>
 __global__ void __launch_bounds__(NT) k_restrict_fine_k(AggMap m, int N, const cx<S>* __restrict__ P, VI in,
                                                         cx<T>* __restrict__ out, long ldi, long ldo, int nr, Mask mk) {
@@ -1571,19 +1575,17 @@ __global__ void __launch_bounds__(NT) k_restrict_fine_k(AggMap m, int N, const c
     const int kper = (N + gridDim.z - 1) / gridDim.z;
     const int k0 = blockIdx.z * kper, k1 = min(N, k0 + kper);
     const int W = KR * 2 * N;   // reduction slots per wave
-    auto row = [&](int k, cx<T> (&q)[12]) {
-        if (act) load_spinor(P + (size_t)min(k, k1 - 1) * 24 * vh, vh, p, i, q);
-        else
+    auto row = [&](int k, cx<S> (&q)[12]) {
 #pragma unroll
-            for (int c = 0; c < 12; c++) q[c] = czero<T>();
+        for (int c = 0; c < 12; c++) q[c] = act ? P[(size_t)k * 24 * vh + (size_t)(p * 12 + c) * vh + i] : czero<S>();
     };
-    cx<T> qn[12];   // the next test vector, in flight during the sums of this one
+    cx<S> qn[12];   // the next test vector, in flight during the sums of this one
     if (k0 < k1) row(k0, qn);
     for (int k = k0; k < k1; k++) {
         cx<T> q[12];
 #pragma unroll
-        for (int c = 0; c < 12; c++) q[c] = qn[c];
-        row(k + 1, qn);
+        for (int c = 0; c < 12; c++) q[c] = ccast<T>(qn[c]);
+        if (k + 1 < k1) row(k + 1, qn);
         double d[4 * KR] = {};   // [r][half][re, im]
 #pragma unroll
         for (int r = 0; r < KR; r++)
