@@ -35,9 +35,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # kernel class -> (kernel name prefixes in the trace, source file); the
 # prefixes cover the FP64 and the FP32 forms of each class
 CLASSES = {
-    "sap": (("void dd::k_sap_fine<double, double, dd::cx<double>*, 1>(",
-             "void dd::k_sap_fine<float, float, dd::cx<float>*, 2>(",
-             "void dd::k_sap_fine<double, double, 1>("), "paper_1303_1377_amd/csrc/dd_fine.hip"),
+    "sap": (("void dd::k_sap_fine<double, double, dd::cx<double>*, false, 1>(",
+             "void dd::k_sap_fine<float, float, dd::cx<float>*, false, 2>("), "paper_1303_1377_amd/csrc/dd_fine.hip"),
     "dirac64": (("void dd::k_dirac<double, double", "void dd::k_dirac_lds<double, double"),
                 "paper_1303_1377_amd/csrc/dd_fine.hip"),
     "restrict": (("void dd::k_restrict_fine<double, double, 256",
