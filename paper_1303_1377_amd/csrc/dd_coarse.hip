@@ -1283,11 +1283,11 @@ void coarse_shift_diag(const Geom& g, int nd, double dm, cx<T>* M, hipStream_t s
 //   z_e -= Minv_e H_int e_o,  z_o += e_o
 // One workgroup per (block, group of KR right-hand sides).
 //
-// Bound: a 2^4 block of nd = 40 applies 470 blocks of nd x nd per half sweep
-// (6 MB in FP32), in 17 dependent phases; nothing of it fits on chip, so the
-// blocks stream from L2 / MALL and a phase is as fast as the loads the
+// Bound: with 4 MR steps a 2^4 block of nd = 40 applies 504 blocks of nd x nd per
+// half sweep (6.5 MB in FP32), in 17 dependent phases; nothing of it fits on chip,
+// so the blocks stream from L2 / MALL and a phase is as fast as the loads the
 // workgroup keeps in flight.  One row per thread (320 threads, 8-byte loads,
-// a serial walk over a site's columns) kept too few: 2.2 TB/s with one
+// a serial walk over a site's columns) kept too few: 2.0 TB/s with one
 // workgroup per CU.  Here a phase is one product with many columns at once:
 // LC = nd / RPL lanes read a block column as 16-byte words (RPL rows per
 // lane), `parts` such lane groups share the panel of one site (group p takes
@@ -1298,9 +1298,9 @@ void coarse_shift_diag(const Geom& g, int nd, double dm, cx<T>* M, hipStream_t s
 // all directions at once (in rounds of `H` where LDS is short); the new z_e is
 // stored before the odd residual reads it, which makes H z + H_int t0 one pass.
 // Per half sweep, before -> now (4 MR steps): 64x32^3 level 1 (16x8^3, nd 40,
-// FP32, 4 RHS) 823 -> 306 us, 5 TB/s; 48x24^3 level 1 (2x3^3 blocks from
-// tables, FP32, 4 RHS) 834 -> 397 us, 6 TB/s; 32x16^3 level 1 (FP16 storage,
-// 1 RHS, 16 workgroups) 253 -> 94 us.
+// FP32, 4 RHS) 812 -> 291 us, 5.7 TB/s; 48x24^3 level 1 (2x3^3 blocks from
+// tables, FP32, 4 RHS) 824 -> 350 us, 6.8 TB/s; 32x16^3 level 1 (FP16 storage,
+// 1 RHS, 16 workgroups) 253 -> 90 us.
 // ---------------------------------------------------------------------------
 static constexpr int CS_NT = 1024;
 static constexpr int CS_PARTS = 12;   // lane groups that share a site's columns, at most
@@ -1702,19 +1702,28 @@ static void coarse_sap_pick(const CoarseOp<T, S>& op, const int* blocks, int nbl
         else if (sh.nv == 2) coarse_sap_go<T, S, KR, RPL, 2>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
         else coarse_sap_go<T, S, KR, RPL, 3>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
     };
-    // the widest group of right-hand sides that fits, shares a block's loads and
-    // still gives the launch about one workgroup for every second CU (24 blocks of
-    // 2x3^3 and 4 RHS: 397 us as 96 workgroups of one RHS, 506 us as 48 of two)
-    auto want = [&](int kr) { return nr > kr / 2 && nblocks * ((nr + kr - 1) / kr) >= 128; };
-    if constexpr (sizeof(T) == 4 && (sizeof(S) != 2 || RPL == 4)) {
-        const SapShape s4 = coarse_sap_shape<T>(bv, op.nd, 4, RPL);
-        if (s4.ok && s4.units >= 6 && want(4)) return launch(std::integral_constant<int, 4>{}, s4);
-    }
-    if constexpr (sizeof(S) != 2 || RPL == 4) {
-        const SapShape s2 = coarse_sap_shape<T>(bv, op.nd, 2, RPL);
-        if (s2.ok && s2.units >= 6 && want(2)) return launch(std::integral_constant<int, 2>{}, s2);
-    }
+    // A group shares a block's loads but is a longer chain in its workgroup: the
+    // narrowest group whose workgroups have a CU each (256), or where even the widest
+    // has more, that one.  Timed for 8 to 256 blocks per colour, 12 to 60 unknowns,
+    // every storage, two to eight RHS.  With a CU for each the wider group takes 1.1
+    // (FP64) to 1.5 times as long: 64 blocks of 2^4, N = 20, FP32, four RHS 118 us
+    // single, 133 in pairs, 196 in fours.  With two rounds the narrower takes up to
+    // twice as long: the same with eight RHS 230 us single, 137 in pairs.  (With few
+    // unknowns two workgroups share a CU and the narrower group would win a round
+    // longer: 128 blocks, N = 8, FP32, four RHS 55 us single, 61 in pairs.)
+    auto groups = [&](int kr) { return nblocks * ((nr + kr - 1) / kr); };
     const SapShape s1 = coarse_sap_shape<T>(bv, op.nd, 1, RPL);
+    if (groups(1) > 256) {
+        if constexpr (sizeof(S) != 2 || RPL == 4) {
+            const SapShape s2 = coarse_sap_shape<T>(bv, op.nd, 2, RPL);
+            if constexpr (sizeof(T) == 4) {
+                const SapShape s4 = coarse_sap_shape<T>(bv, op.nd, 4, RPL);
+                if (nr > 2 && s4.ok && s4.units >= 6 && (groups(2) > 256 || !s2.ok))
+                    return launch(std::integral_constant<int, 4>{}, s4);
+            }
+            if (nr > 1 && s2.ok) return launch(std::integral_constant<int, 2>{}, s2);
+        }
+    }
     if (s1.ok) return launch(std::integral_constant<int, 1>{}, s1);
     const SapShape sb = coarse_sap_shape<T>(bv, op.nd, 1, RPL, true);
     if (!sb.ok) throw std::invalid_argument("coarse SAP block too large for one workgroup");
