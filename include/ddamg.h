@@ -268,7 +268,11 @@ typedef enum {
 /* Apply one component.  in/out are device complex128 vectors of the level in
  * the canonical layout (sizes given by dd_level_info).  `arg` is the number
  * of SAP iterations for DD_OP_SAP and unused otherwise.  Returns the
- * iteration count of solver components in *iters when iters != NULL. */
+ * iteration count of solver components in *iters when iters != NULL.
+ * On a context that dd_configure has not been called on, DD_OP_D at level 0 is
+ * available; its first call allocates two FP64 spinors (384 bytes per site
+ * in all, counted by dd_device_bytes), which the context keeps until
+ * dd_configure or dd_destroy.  dd_apply_D_noalloc needs no such memory. */
 dd_status dd_apply(dd_ctx *ctx, int op, int level, int arg, const double *in, double *out, long *iters);
 
 /* dd_apply on k vectors at once (1 <= k <= max_rhs), run as one batch: the

@@ -318,8 +318,8 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // (the neighbour, the other pair, the mirrored quad and half row, each holding
 // one value by then), then the four row sums by lane reads.  All on the vector
 // unit: the shuffle form took twelve LDS permutes and their latency per FP64
-// sum (64x32^3 restriction of four right-hand sides, 320 sums per wave: 1671 ->
-// 1330 us).  All 64 lanes must be active.
+// sum (64x32^3 restriction of four right-hand sides, 320 sums per wave: 1576 ->
+// 1170 us).  All 64 lanes must be active.
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
     v += dpp_move<0xB1>(v);    // quad_perm [1, 0, 3, 2]
