@@ -41,7 +41,22 @@ def parts(tmp_path_factory):
 #define __device__
 template <class T> struct cx { T re, im; };
 %s%s%s
-int main(int, char** a) {
+template <class T> void refused() {
+    for (int nd = 2; nd <= 64; nd += 2)
+        for (int bv = 1; bv * nd <= 2048; bv++)
+            for (int rpl = 1; rpl <= 4; rpl *= 2) {
+                if (nd %% rpl || (sizeof(T) == 8 && rpl > 1)) continue;
+                const SapShape s = coarse_sap_shape<T>(bv, nd, 1, rpl), b = coarse_sap_shape<T>(bv, nd, 1, rpl, true);
+                const SapShape& c = s.ok ? s : b;
+                if (!c.ok || c.lds > 160 * 1024 || c.parts < 1 || c.hops < 1 || (long)c.nt * c.nv < (long)bv * nd) printf("%%d x %%d ", bv, nd);
+            }
+}
+int main(int n, char** a) {
+    if (n == 1) {
+        refused<double>();
+        refused<float>();
+        return 0;
+    }
     const int bv = atoi(a[2]), nd = atoi(a[3]), kr = atoi(a[4]), rpl = atoi(a[5]);
     const SapShape s = atoi(a[1]) == 8 ? coarse_sap_shape<double>(bv, nd, kr, rpl) : coarse_sap_shape<float>(bv, nd, kr, rpl);
     printf("%%d", s.ok ? s.parts : 0);
@@ -49,11 +64,16 @@ int main(int, char** a) {
 """ % (const, cols, body))
     exe = str(d / "m")
     subprocess.run([CLANG, "-std=c++17", "-O1", "-w", "-o", exe, str(d / "m.cpp")], check=True)
-    return lambda shape: int(subprocess.run([exe, *map(str, shape)], check=True, capture_output=True, text=True).stdout)
+    return lambda *shape: subprocess.run([exe, *map(str, shape)], check=True, capture_output=True, text=True).stdout
 
 
 @pytest.mark.parametrize("shape", list(TIMED), ids=str)
 def test_parts(parts, shape):
-    p, us = parts(shape), TIMED[shape]
+    p, us = int(parts(*shape)), TIMED[shape]
     assert 1 <= p <= len(us)
     assert us[p - 1] <= 1.1 * min(us), "%d parts: %.1f us, the fastest takes %.1f" % (p, us[p - 1], min(us))
+
+
+def test_every_admitted_block_has_a_shape(parts):
+    """configure admits blocks of up to 2048 rows of one parity."""
+    assert parts() == ""
