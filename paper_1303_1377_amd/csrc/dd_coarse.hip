@@ -55,7 +55,8 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
             return;
         }
     }
-    if (!wg_enter<FOLD>(mk, blockIdx.y, run)) return;
+    const bool early = wg_enter<FOLD>(mk, blockIdx.y, run);
+    if (!FOLD && !early) return;
     {
         const long off = blockIdx.y * ld;
         if (in1) in1 += off;
@@ -96,7 +97,6 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
         for (int u = 0; u < CA_PRE; u++)
             a[u] = (row && qb + u < q1) ? A[(size_t)(qb + u) * nd] : cx<S>{S(0), S(0)};
     };
-    load_pairs(q0);
     const int per2 = (nd + nw - 1) / nw;
     const int c0 = w * per2, c1 = min(nd, c0 + per2);
     const cx<S>* Ainv = op.Minv + gs * nn + r;
@@ -107,15 +107,22 @@ __global__ void __launch_bounds__(64 * CA_WAVES) k_coarse_apply(CoarseOp<T, S> o
         for (int u = 0; u < CA_INV; u++)
             b[u] = (row && cb + u < c1) ? Ainv[(size_t)(cb + u) * nd] : cx<S>{S(0), S(0)};
     };
-    if (post_inv) load_inv(c0);
     T f1 = T(1), f2 = T(hop_sign < 0 ? -1 : 1);
-    if (isc.st) {
-        const T f = T(FOLD ? gm_factor(isc, blockIdx.y) : isc.st[blockIdx.y].sc[isc.j]);
-        if (isc.which & 1) f1 *= f;
-        if (isc.which & 2) f2 *= f;
-    }
+    auto ahead = [&]() {   // in flight while the inputs are staged
+        load_pairs(q0);
+        if (post_inv) load_inv(c0);
+        if (isc.st) {
+            const T f = T(FOLD ? gm_factor(isc, blockIdx.y) : isc.st[blockIdx.y].sc[isc.j]);
+            if (isc.which & 1) f1 *= f;
+            if (isc.which & 2) f2 *= f;
+        }
+    };
+    if (early) ahead();
     __syncthreads();
-    if (FOLD && !run) return;
+    if constexpr (FOLD) {
+        if (!run) return;
+        if (!early) ahead();
+    }
     for (int e = threadIdx.x; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
         X[e] = ((s2 >= nself) ? f2 : f1) * vin[s2][e - s2 * nd];
@@ -628,7 +635,8 @@ __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par,
             return;
         }
     }
-    if (!wg_enter<FOLD>(mk, blockIdx.y, run)) return;
+    const bool early = wg_enter<FOLD>(mk, blockIdx.y, run);
+    if (!FOLD && !early) return;
     {
         const long off = blockIdx.y * ld;
         if (in1) in1 += off;
@@ -672,17 +680,23 @@ __global__ void __launch_bounds__(256) k_coarse_rows(CoarseOp<T, S> op, int par,
             a[u] = (rok && q < Q) ? A[(size_t)q * nd] : cx<S>{S(0), S(0)};
         }
     };
-    load(qs);   // in flight while the inputs are staged
     // factors of the two inputs (stored GMRES basis vectors carry theirs in the state)
     T f1 = T(1), f2 = T(1);
-    if (isc.st) {
-        const T f = T(FOLD ? gm_factor(isc, blockIdx.y) : isc.st[blockIdx.y].sc[isc.j]);
-        if (isc.which & 1) f1 = f;
-        if (isc.which & 2) f2 = f;
-    }
-    if (hop_sign < 0) f2 = -f2;
+    auto ahead = [&]() {   // in flight while the inputs are staged
+        load(qs);
+        if (isc.st) {
+            const T f = T(FOLD ? gm_factor(isc, blockIdx.y) : isc.st[blockIdx.y].sc[isc.j]);
+            if (isc.which & 1) f1 = f;
+            if (isc.which & 2) f2 = f;
+        }
+        if (hop_sign < 0) f2 = -f2;
+    };
+    if (early) ahead();
     __syncthreads();
-    if (FOLD && !run) return;
+    if constexpr (FOLD) {
+        if (!run) return;
+        if (!early) ahead();
+    }
     for (int e = t; e < Q; e += blockDim.x) {
         const int s2 = e / nd;
         const cx<T> v = vin[s2][e - s2 * nd];

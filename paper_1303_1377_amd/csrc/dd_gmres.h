@@ -79,16 +79,17 @@ __device__ __forceinline__ void gm_column_wg(GmDev* st, int j, const cx<double>*
     }
 }
 
-// Whether the workgroup works on right-hand side r.  Beside a fold the flag may be
-// raised while the launch runs and the waves would read it before and after: one
-// thread then reads it for all, and the workgroup takes the decision from `run`
-// behind its first barrier.  (Waves that went on without the others would read
-// input pointers in LDS that nobody had stored.)
+// Whether this wave sees right-hand side r running (the same in all its lanes).
+// Beside a fold the flag may be raised while the launch runs, so the waves of a
+// workgroup may differ: one thread's reading, kept in `run`, decides for all behind
+// the first barrier, and no wave leaves before it.  (Waves that went on without the
+// others would read input pointers in LDS that nobody had stored.)  What a wave
+// asks for ahead of the barrier goes by its own reading.
 template <bool FOLD>
 __device__ __forceinline__ bool wg_enter(const Mask& mk, int r, int& run) {
-    if constexpr (!FOLD) return mk.on(r);
-    if (threadIdx.x == 0) run = mk.on(r);
-    return true;
+    const int on = __builtin_amdgcn_readfirstlane((int)mk.on(r));
+    if (FOLD && threadIdx.x == 0) run = on;
+    return on != 0;
 }
 
 // The extra workgroup of the first kernel of a step: column isc.j - 1 of

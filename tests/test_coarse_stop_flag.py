@@ -97,6 +97,7 @@ inline void __syncthreads() { emu::wait(emu::GROUP); }
 template <class T> T __shfl_xor(T v, int m, int) { return emu::from_lane(v, (emu::cur & 63) ^ m); }
 #define __builtin_amdgcn_mov_dpp(v, ctrl, ...) emu::dpp(v, ctrl)
 #define __builtin_amdgcn_readlane(v, l) emu::from_lane((int)(v), l)
+#define __builtin_amdgcn_readfirstlane(v) emu::from_lane((int)(v), 0)
 struct Swap2 { unsigned v[2]; unsigned operator[](int i) const { return v[i]; } };
 #define __builtin_amdgcn_permlane32_swap(a, b, ...) Swap2{{a, b}}
 #define __builtin_amdgcn_permlane16_swap(a, b, ...) Swap2{{a, b}}
