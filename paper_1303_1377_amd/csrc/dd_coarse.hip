@@ -1311,9 +1311,16 @@ void coarse_shift_diag(const Geom& g, int nd, double dm, cx<T>* M, hipStream_t s
 // aligned read per column for all KR.  The hops of the residual are staged for
 // all directions at once (in rounds of `H` where LDS is short); the new z_e is
 // stored before the odd residual reads it, which makes H z + H_int t0 one pass.
+// Rounding: a lane adds one long chain, so the order counts.  The site's own block is
+// by far the largest term and comes after the hops; first, every hop was rounded
+// at its size, and the FP32 error of a sweep against FP64 was 2.25e-7 (2^4, nd 40)
+// instead of 9.8e-8 (1.30e-7 with a sum per block).  FOLD: with one or two
+// lane groups the chain is so long that a batch of columns is summed by itself (2x3^3,
+// nd 64: 2.11e-7 without, 1.07e-7 with; 1.57e-7 with a sum per block).  16-bit storage
+// has errors of 2^-11 and takes no fold.
 // Per half sweep, before -> now (4 MR steps): 64x32^3 level 1 (16x8^3, nd 40,
-// FP32, 4 RHS) 812 -> 291 us, 5.7 TB/s; 48x24^3 level 1 (2x3^3 blocks from
-// tables, FP32, 4 RHS) 824 -> 350 us, 6.8 TB/s; 32x16^3 level 1 (FP16 storage,
+// FP32, 4 RHS) 812 -> 287 us, 5.8 TB/s; 48x24^3 level 1 (2x3^3 blocks from
+// tables, FP32, 4 RHS) 824 -> 349 us, 6.8 TB/s; 32x16^3 level 1 (FP16 storage,
 // 1 RHS, 16 workgroups) 253 -> 90 us.
 // ---------------------------------------------------------------------------
 static constexpr int CS_NT = 1024;
@@ -1331,12 +1338,13 @@ template <class T, int KR> struct alignas(sizeof(cx<T>) * KR > 16 ? 16 : sizeof(
 // fit in LDS beside the fields: neighbours are found again where they are read, and
 // the staged hops take no fields of their own.  Three fields and 48 bytes per site
 // then hold every block of 2048 rows (1024 sites of 2 unknowns in FP64: 144 KB)
-template <class T, class S, int KR, int RPL, int NV, bool BIG>
+template <class T, class S, int KR, int RPL, int NV, bool BIG, bool FOLD>
 __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const int* __restrict__ blocks, SapTab tab, int bv,
                                                       const cx<T>* __restrict__ b, cx<T>* __restrict__ z, int mr_steps,
                                                       long ld, int nr, Mask mk, int parts, int H) {
     using RP = RowPack<S, RPL>;
-    using XP = RhsPack<T, KR>;
+    constexpr int XQ = FOLD && KR * sizeof(cx<T>) > 16 ? 16 / sizeof(cx<T>) : KR;
+    using XP = RhsPack<T, XQ>;
     const int q0 = blockIdx.y * KR;
     unsigned on = 0;
 #pragma unroll
@@ -1439,14 +1447,40 @@ __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const i
                 return m;
             };
             auto use = [&](const RP (&a)[U], int xo, int m) {
+                if constexpr (FOLD) {
+                    // the batch by itself, XQ right-hand sides at a time
 #pragma unroll
-                for (int u = 0; u < U; u++) {
-                    const XP x = *reinterpret_cast<const XP*>(so + (u < m ? xo + u * (parts * KR) : (int)(zero - so)));
+                    for (int q1 = 0; q1 < KR; q1 += XQ) {
+                        cx<T> sum[RPL][XQ];
 #pragma unroll
-                    for (int r = 0; r < RPL; r++) {
-                        const cx<T> ar = ccast<T>(a[u].v[r]);
+                        for (int r = 0; r < RPL; r++)
 #pragma unroll
-                        for (int q = 0; q < KR; q++) cmac(acc[r][q], ar, x.v[q]);
+                            for (int q = 0; q < XQ; q++) sum[r][q] = czero<T>();
+#pragma unroll
+                        for (int u = 0; u < U; u++) {
+                            const XP x = *reinterpret_cast<const XP*>(so + (u < m ? xo + u * (parts * KR) + q1 : (int)(zero - so)));
+#pragma unroll
+                            for (int r = 0; r < RPL; r++) {
+                                const cx<T> ar = ccast<T>(a[u].v[r]);
+#pragma unroll
+                                for (int q = 0; q < XQ; q++) cmac(sum[r][q], ar, x.v[q]);
+                            }
+                        }
+#pragma unroll
+                        for (int r = 0; r < RPL; r++)
+#pragma unroll
+                            for (int q = 0; q < XQ; q++) acc[r][q1 + q] += sum[r][q];
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; u++) {
+                        const XP x = *reinterpret_cast<const XP*>(so + (u < m ? xo + u * (parts * KR) : (int)(zero - so)));
+#pragma unroll
+                        for (int r = 0; r < RPL; r++) {
+                            const cx<T> ar = ccast<T>(a[u].v[r]);
+#pragma unroll
+                            for (int q = 0; q < KR; q++) cmac(acc[r][q], ar, x.v[q]);
+                        }
                     }
                 }
             };
@@ -1489,10 +1523,12 @@ __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const i
             if (t + u * nt < F) f[t + u * nt] = sgn * s[u];
         __syncthreads();
     };
-    // s += sum over the slots [s0, 9) of the sites of parity p applied to z (slot 0: the site itself)
+    // s += sum over the slots [s0, 9) of the sites of parity p applied to z, from the last
+    // to the first (slot 0: the site itself)
     auto outer = [&](int p, int s0, cx<T> (&s)[NV]) {
-        for (int sa = s0; sa < 9; sa += H) {
-            const int ns = min(H, 9 - sa);
+        for (int end = 9, sa; end > s0; end = sa) {
+            sa = max(s0, end - H);
+            const int ns = end - sa;
             // SU entries per thread are loaded before the first is stored
             constexpr int SU = 4;
             for (int e0 = t; e0 < ns * F; e0 += SU * nt) {
@@ -1522,24 +1558,24 @@ __global__ void __launch_bounds__(CS_NT) k_coarse_sap(CoarseOp<T, S> op, const i
             product([&](int l) { return op.M + (((size_t)p * g.vh + sidx[p * bv + l]) * 9 + sa) * nn; },
                     [&](int) { return ns; },
                     [&](int l, int e, int& slot, int& x0) {
-                        slot = e;
-                        x0 = (int)(sg - so) + (e * bv + l) * nd * KR;
+                        slot = ns - 1 - e;
+                        x0 = (int)(sg - so) + (slot * bv + l) * nd * KR;
                     });
             gather(s);
             __syncthreads();   // the staged inputs and the partial rows are free again
         }
     };
-    // s += [M0 f0 +] sum of the inner hops of parity p applied to the field f
+    // s += sum of the inner hops of parity p applied to the field f, then M0 f0 where there is f0
     auto inner = [&](int p, const cx<T>* f0, const cx<T>* f, cx<T> (&s)[NV]) {
         const int o0 = f0 ? (int)(f0 - so) : 0, o1 = (int)(f - so), self = f0 ? 1 : 0;
         product([&](int l) { return op.M + ((size_t)p * g.vh + sidx[p * bv + l]) * 9 * nn; },
                 [&](int l) { return self + cnt[p * bv + l]; },
                 [&](int l, int e, int& slot, int& x0) {
-                    if (e < self) {
+                    if (e == cnt[p * bv + l]) {
                         slot = 0;
                         x0 = o0 + l * nd * KR;
                     } else {
-                        const int w = lst[(p * bv + l) * 8 + e - self];
+                        const int w = lst[(p * bv + l) * 8 + e];
                         slot = w & 15;
                         x0 = o1 + (w >> 4) * nd * KR;
                     }
@@ -1664,7 +1700,9 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
     // 4^4; 4 to 60 unknowns; every storage; one and eight right-hand sides; all parts):
     // 2 % above the best parts in the mean, 22 % at most.  The fewest rounds alone
     // were 11 % above in the mean and up to 2.1 times: LDS left for one staged hop, or
-    // batches half empty.
+    // batches half empty.  Few unknowns take two parts wherever these are one round:
+    // a single part adds a site's last columns one after another at full size (FP32,
+    // N = 2, 4^2x2^2: error 7.59e-8 against 7.14e-8; time the same within 4 %)
     const int u = coarse_sap_cols(sizeof(T), rpl * kr);
     double best = 0;
     for (int p = 1; p <= CS_PARTS && p < s.units + big && p <= nd; p++) {
@@ -1677,7 +1715,7 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
         const int rounds = (bv * p + groups - 1) / groups, staged = (9 + hops - 1) / hops + (8 + hops - 1) / hops;
         const double cost = rounds * ((columns + u - 1) / u + 0.05 * columns) + 0.1 * staged +
                             0.05 * p * ((f + nt - 1) / nt) + 0.05 * nt / 256;
-        if (p > 1 && cost >= best) continue;
+        if (p > 1 && cost >= best && !(p == 2 && nd < 12 && bv * p * lc <= CS_NT)) continue;
         best = cost;
         s.parts = p;
         s.hops = hops;
@@ -1689,7 +1727,7 @@ static SapShape coarse_sap_shape(int bv, int nd, int kr, int rpl, bool big = fal
     return s;
 }
 
-template <class T, class S, int KR, int RPL, int NV, bool BIG = false>
+template <class T, class S, int KR, int RPL, int NV, bool BIG, bool FOLD>
 static void coarse_sap_go(const CoarseOp<T, S>& op, const int* blocks, int nblocks, SapTab tab, int bv, const cx<T>* b,
                           cx<T>* z, int mr_steps, hipStream_t s, int nr, long ld, Mask mk, const SapShape& sh) {
     static std::mutex mu;
@@ -1697,12 +1735,12 @@ static void coarse_sap_go(const CoarseOp<T, S>& op, const int* blocks, int nbloc
     {
         std::lock_guard<std::mutex> lock(mu);
         // a refusal leaves its error for the launch below to report
-        if (sh.lds > configured && hipFuncSetAttribute((const void*)k_coarse_sap<T, S, KR, RPL, NV, BIG>,
+        if (sh.lds > configured && hipFuncSetAttribute((const void*)k_coarse_sap<T, S, KR, RPL, NV, BIG, FOLD>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds) == hipSuccess)
             configured = sh.lds;
     }
     dim3 grid(nblocks, (nr + KR - 1) / KR);
-    k_coarse_sap<T, S, KR, RPL, NV, BIG><<<grid, sh.nt, sh.lds, s>>>(op, blocks, tab, bv, b, z, mr_steps, ld, nr, mk, sh.parts,
+    k_coarse_sap<T, S, KR, RPL, NV, BIG, FOLD><<<grid, sh.nt, sh.lds, s>>>(op, blocks, tab, bv, b, z, mr_steps, ld, nr, mk, sh.parts,
                                                                sh.hops);
 }
 
@@ -1710,11 +1748,20 @@ template <class T, class S, int RPL>
 static void coarse_sap_pick(const CoarseOp<T, S>& op, const int* blocks, int nblocks, SapTab tab, const cx<T>* b, cx<T>* z,
                             int mr_steps, hipStream_t s, int nr, long ld, Mask mk) {
     const int bv = tab.bv ? tab.bv : op.g.bvh;
+    auto go = [&](auto kr, auto nv, auto big, const SapShape& sh) {
+        constexpr int KR = decltype(kr)::value, NV = decltype(nv)::value;
+        constexpr bool BIG = decltype(big)::value;
+        // fewer unknowns gain nothing by it (2x3^3, N = 2: 1.00 of the error with a sum per
+        // block without, 1.03 with)
+        if constexpr (sizeof(S) > 2)
+            if (sh.parts <= 2 && op.nd >= 12)
+                return coarse_sap_go<T, S, KR, RPL, NV, BIG, true>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
+        coarse_sap_go<T, S, KR, RPL, NV, BIG, false>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
+    };
     auto launch = [&](auto kr, const SapShape& sh) {
-        constexpr int KR = decltype(kr)::value;
-        if (sh.nv == 1) coarse_sap_go<T, S, KR, RPL, 1>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
-        else if (sh.nv == 2) coarse_sap_go<T, S, KR, RPL, 2>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
-        else coarse_sap_go<T, S, KR, RPL, 3>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sh);
+        if (sh.nv == 1) go(kr, std::integral_constant<int, 1>{}, std::false_type{}, sh);
+        else if (sh.nv == 2) go(kr, std::integral_constant<int, 2>{}, std::false_type{}, sh);
+        else go(kr, std::integral_constant<int, 3>{}, std::false_type{}, sh);
     };
     // A group shares a block's loads but is a longer chain in its workgroup: the
     // narrowest group whose workgroups have a CU each (256), or where even the widest
@@ -1741,7 +1788,7 @@ static void coarse_sap_pick(const CoarseOp<T, S>& op, const int* blocks, int nbl
     if (s1.ok) return launch(std::integral_constant<int, 1>{}, s1);
     const SapShape sb = coarse_sap_shape<T>(bv, op.nd, 1, RPL, true);
     if (!sb.ok) throw std::invalid_argument("coarse SAP block too large for one workgroup");
-    coarse_sap_go<T, S, 1, RPL, 3, true>(op, blocks, nblocks, tab, bv, b, z, mr_steps, s, nr, ld, mk, sb);
+    go(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{}, std::true_type{}, sb);
 }
 
 template <class T, class S>
